@@ -82,8 +82,9 @@ enum { /* support kinds */
   MTO_SUP_EDGE_TOP = 4     /* y = nely */
 };
 
-enum { /* element contraction kernels */
-  MTO_PATH_MFMA = 0,  /* per-(p,d) group, FP64 MFMA tiles (default) */
+enum { /* element product kernels */
+  MTO_PATH_MFMA = 0,  /* per (p, d) group: the sum-factorised product, or the dense contraction on
+                         FP64 MFMA tiles, chosen by mto_set_tile or mto_autotune (default) */
   MTO_PATH_PLAIN = 1  /* one thread per element column, FP64 VALU (comparison path) */
 };
 
@@ -318,8 +319,9 @@ int mto_weighted_sensitivity(mto_plan* plan, const double* g, const double* w, d
  * first load case (length sum_i n_dof_i); supported DOFs get 0. */
 int mto_jacobi_diagonal(mto_plan* plan, const double* rho, double* diag, void* stream);
 
-/* Times the element contraction of every (p, d) group of the plan for each
- * tile shape (ncol x ks, see mto_set_tile) and keeps the fastest per group.  rho is a
+/* Times the element product of every (p, d) group of the plan for each
+ * tile shape (ncol x ks, see mto_set_tile; the sum-factorised product
+ * included) and keeps the fastest per group.  rho is a
  * representative density field.  cache_path (host string, may be NULL): a
  * text file of tile shapes keyed by (GPU architecture, p, d, floor(log2 of
  * the group's element columns)); a group found there takes the cached
@@ -332,16 +334,20 @@ int mto_jacobi_diagonal(mto_plan* plan, const double* rho, double* diag, void* s
 int mto_autotune(mto_plan* plan, const double* rho, const char* cache_path, void* stream, char* report,
                  int32_t report_len);
 
-/* Sets the tile shape of the element contraction for the group with order p
- * and cell grid d (all groups if p <= 0): ncol blocks of 16 element columns
+/* Sets the kernel and tile shape of the element product for the group with
+ * order p and cell grid d (all groups if p <= 0).  A new plan takes ks = -3
+ * for every group: the sum-factorised product (ncol ignored), which uses the
+ * tensor structure of the basis and of the cell grid instead of the dense
+ * cell tables, every such group in one launch.  The dense contraction:
+ * ncol blocks of 16 element columns
  * per tile (1, 2 or 4) and ks waves per tile splitting the density cells
  * (1..8, clamped to d*d); or, with ks = 0 (p >= 3 only, ncol 1 or 2), the
  * LDS-staged contraction: 4 waves of 16 ncol columns each share the cell
  * tables, staged in LDS one cell ahead (with p <= 0 the groups of p < 3 keep
  * their shape).  ks = -1 (p, d, ncol ignored): the product of every group in
  * one launch (the LDS-staged contraction of 64-column tiles from all groups,
- * the long ones first); any other call returns to one launch per group.
- * mto_autotune picks between the two by timing.  ks = -2 (ncol ignored):
+ * the long ones first); any other call returns to the groups' own choices.
+ * mto_autotune picks among all of these by timing.  ks = -2 (ncol ignored):
  * stored element matrices for the group(s): K_e = sum_s E_s K_s (the
  * operator of Eq. (2) with the composite integration of Appendix B, per
  * element) is assembled once per solve set-up and mto_apply_stiffness call,

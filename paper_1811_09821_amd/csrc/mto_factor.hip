@@ -1,0 +1,370 @@
+// Element product by sum factorisation: y_e = sum_s E_{e,s} K_s u_e without
+// the dense cell tables K_s.
+//
+// The basis is a tensor product and the cells of an element form a d x d
+// grid, so every K_s is a sum of products of 1D integrals over one cell
+// interval, a(i,k) = int phi_i' phi_k', b(i,k) = int phi_i phi_k,
+// c(i,k) = int phi_i' phi_k (unit interval, n = p + 1 functions):
+//   K_s[x,x] = D11 a_x b_y + D33 b_x a_y      K_s[x,y] = D12 c_x c_y^T + D33 c_x^T c_y
+//   K_s[y,y] = D11 b_x a_y + D33 a_x b_y      K_s[y,x] = D12 c_x^T c_y + D33 c_x c_y^T
+// For one row sy of cells the moduli enter the x factors only, M_t = sum_sx
+// E[sx, sy] t_x^(sx) for t = a, b, c, after which the row costs two small
+// matrix products (along x, then along y): d (8 n^3 + 8 n^3 + (2 n^2 + n) d)
+// multiply-adds per element against d^2 (2 n^2)^2 for the dense contraction,
+// 11.4 k against 62.5 k at p = 4, d = 5 and 4.7 k against 16.4 k at p = 3, d = 4.
+//
+// One lane takes one element column, so the 1D tables are the same for every
+// lane: they come through the scalar cache and enter the FMAs as scalar
+// operands, and no lane idles on padding.  Per lane: 2 n^2 accumulators in
+// registers, the element vector in LDS ([row][lane], conflict free).  FP64
+// vector FMAs run at the FP64 MFMA rate on gfx950, so nothing is lost by
+// leaving the matrix cores, whose 16 x 16 tiles fit neither the 5 x 5 factors
+// nor a per-element operand.
+//
+// The cell rows form fac_chains(d) chains (rows ch, ch + chains, ...), each
+// summed in one accumulator, and the chains' sums are added in order: the
+// same rounding however the work is split, so a design's results do not
+// depend on what else is in its plan.  A split tile gives its 64 columns to a
+// block of W waves, one chain (or, with waves to spare, one component of one
+// chain) to a wave, which share the gather and the scatter and meet in LDS.
+// The other tiles (small elements of large meshes) go one to a wave, from
+// gather to scatter without a barrier, W of them to a block.
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "mto_device.hpp"
+#include "mto_kernels.hpp"
+
+namespace mto {
+namespace {
+
+typedef const __attribute__((address_space(4))) double* cptr;  // read-only tables, through the scalar cache
+__device__ __forceinline__ cptr scalar_table(const double* p) { return (cptr)(uintptr_t)p; }
+
+typedef const __attribute__((address_space(3))) double* lds_vec;
+
+__host__ __device__ constexpr int sym_index(int n, int i, int k) {  // packed upper triangle by rows
+  return i <= k ? i * n - i * (i - 1) / 2 + (k - i) : k * n - k * (k - 1) / 2 + (i - k);
+}
+
+// acc += the product for the cell rows sy0, sy0 + step, ... of one column: u
+// its element vector in LDS (rigid motion removed; row r at 64 r), tab the
+// group's 1D tables.  NC = 2: both components; NC = 1: component c0 alone.
+// NK < n: u is nonzero only for the functions i, j < NK (the vertex
+// functions, NK = 2).
+// A single wave issues one instruction in 4 cycles whatever its kind, so the
+// input rows are unrolled (no register moves, no loop control) with the next
+// row's LDS and table reads ahead of the current one's products.  The empty
+// asm statements hold each pass together: without them the compiler keeps u
+// in registers across the passes, or sinks a pass's products below the next
+// loop with all their operands live, and spills.
+template <int P, int NK, int NC>
+__device__ __forceinline__ void factored_rows(int d, cptr tab, const double* __restrict__ Ecell, int sy0, int step,
+                                              int c0, lds_vec u, double (&acc)[NC][P + 1][P + 1]) {
+  constexpr int n = P + 1, NS = n * (n + 1) / 2, XT = fac_x_of(P), YT = fac_y_of(P);
+  cptr yt = tab + d * XT;
+#pragma unroll 1
+  for (int sy = sy0; sy < d; sy += step) {
+    cptr ys = yt + sy * n * YT;
+    const double* __restrict__ Er = Ecell + sy * d;
+    // M = sum_sx E t^(sx) for NM table entries from `off` on
+    auto moduli = [&](auto& M, int off) {
+      constexpr int NM = sizeof(M) / sizeof(double);
+      double e = Er[0];
+#pragma unroll
+      for (int q = 0; q < NM; ++q) M[q] = 0.0;
+#pragma unroll 1
+      for (int sx = 0; sx < d; ++sx) {
+        const double en = Er[min(sx + 1, d - 1)];
+        cptr x = tab + sx * XT + off;
+#pragma unroll
+        for (int q = 0; q < NM; ++q) M[q] = fma(x[q], e, M[q]);
+        e = en;
+      }
+    };
+    // acc[c] += y_c (m u_c) along x, then y; entry(i, k) the x matrix, y
+    // columns yo and yo + 1 for the components; `swap`: the other component's u
+    auto pass = [&](int yo, bool swap, auto entry) {
+      lds_vec up = u;
+      asm volatile("" : "+v"(up));
+      if (NC == 1) up += 64 * (swap ? 1 - c0 : c0);
+      cptr yc = ys + (NC == 1 ? yo + c0 : yo) * n;
+      double ul[2][NK][NC], yv[2][NC][n];
+      auto request = [&](int b, int l) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c)
+#pragma unroll
+          for (int j = 0; j < n; ++j) yv[b][c][j] = yc[l * YT + c * n + j];
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+          for (int c = 0; c < NC; ++c) ul[b][k][c] = up[(2 * (l * n + k) + c) * 64];
+      };
+      request(0, 0);
+#pragma unroll
+      for (int l = 0; l < NK; ++l) {
+        const int b = l & 1;
+        if (l + 1 < NK) request(b ^ 1, l + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        double T[NC][n];
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+#pragma unroll
+          for (int i = 0; i < n; ++i)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              T[c][i] = k == 0 ? entry(i, k) * ul[b][0][c] : fma(entry(i, k), ul[b][k][c], T[c][i]);
+#pragma unroll
+        for (int j = 0; j < n; ++j)
+#pragma unroll
+          for (int i = 0; i < n; ++i)
+#pragma unroll
+            for (int c = 0; c < NC; ++c)
+              acc[c][j][i] = fma(yv[b][c][j], T[NC == 2 && swap ? 1 - c : c][i], acc[c][j][i]);
+      }
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int a = 0; a < n * n; ++a) asm volatile("" : "+v"(acc[c][a / n][a % n]));
+    };
+    // a_x: D11 b_y on x, D33 b_y on y; b_x: D33 a_y on x, D11 a_y on y; c_x and
+    // its transpose couple the components.  The three x matrices are formed
+    // together where the registers hold them.
+    if constexpr (P <= 3) {
+      double M[2 * NS + n * n];
+      moduli(M, 0);
+      pass(0, false, [&](int i, int k) { return M[sym_index(n, i, k)]; });
+      pass(2, false, [&](int i, int k) { return M[NS + sym_index(n, i, k)]; });
+      pass(4, true, [&](int i, int k) { return M[2 * NS + i * n + k]; });
+      pass(6, true, [&](int i, int k) { return M[2 * NS + k * n + i]; });
+    } else {
+      {
+        double M[2 * NS];
+        moduli(M, 0);
+        pass(0, false, [&](int i, int k) { return M[sym_index(n, i, k)]; });
+        pass(2, false, [&](int i, int k) { return M[NS + sym_index(n, i, k)]; });
+      }
+      double C[n * n];
+      moduli(C, 2 * NS);
+      pass(4, true, [&](int i, int k) { return C[i * n + k]; });
+      pass(6, true, [&](int i, int k) { return C[k * n + i]; });
+    }
+  }
+}
+
+template <int P, int NC>
+__device__ __forceinline__ void clear(double (&acc)[NC][P + 1][P + 1]) {
+#pragma unroll
+  for (int c = 0; c < NC; ++c)
+#pragma unroll
+    for (int a = 0; a < (P + 1) * (P + 1); ++a) acc[c][a / (P + 1)][a % (P + 1)] = 0.0;
+}
+
+// One tile by the W waves of a block (SPLIT), or by one wave (W = 1, no
+// barrier); ush: its LDS, [NE][64] element vectors, then partial results.
+template <int P, bool SPLIT>
+__device__ __forceinline__ void factored_tile(const FacTile& t, const double* __restrict__ E,
+                                              const double* __restrict__ xin, const PcgDev& s, int mode, int it_k,
+                                              double* ush) {
+  constexpr int n = P + 1, NE = ne_of(P);
+  // a stopped system has nothing to do (PCG mode also checks this iteration's residual below)
+  if (mode != ELEM_APPLY && s.status[t.sys] != SYS_RUNNING) return;
+  const bool pcg = mode == ELEM_PCG;
+  const int W = SPLIT ? blockDim.x >> 6 : 1, lane = threadIdx.x & 63;
+  const int wave = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+  const bool valid = lane < t.count;
+  const int el = valid ? lane : t.count - 1;  // idle lanes repeat the last column, unstored
+  const double* __restrict__ xs = xin + t.dof_off;
+  const double* __restrict__ zs = s.z + t.dof_off;
+  const int32_t* __restrict__ gi_ = t.gidx + el;
+  const int cell = t.cell[el];
+  // the column's moduli, one read per cache line: on their way during the gather
+  double warm[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) warm[k] = E[cell + min(16 * k, t.d * t.d - 1)];
+  // Rows wave, wave + W, ...: GB index loads, then their values, all
+  // unconditional (clamped row; an absent DOF reads the system's first).
+  // Every wave reduces the PCG scalars itself, while its first values load: no
+  // barrier, and no memory round trip more than the values take.
+  double beta = 0.0;
+  bool on = true;
+  {
+    constexpr int GB = SPLIT ? (NE + 3) / 4 : (NE + 1) / 2;
+    int gi[GB];
+    for (int r0 = wave; r0 < NE; r0 += W * GB) {
+#pragma unroll
+      for (int q = 0; q < GB; ++q) gi[q] = gi_[(int64_t)min(r0 + W * q, NE - 1) * t.npad];
+      const int it = pcg && r0 == wave ? *s.it_base + it_k : 0;
+      double v[GB], z[GB];
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        const int gc = max(gi[q], 0);
+        v[q] = xs[gc];
+        z[q] = pcg ? zs[gc] : 0.0;
+      }
+      if (pcg && r0 == wave) {
+        const Scal sc = pcg_state(s, t.sys, t.pc_begin, t.pc_end, it, true);
+        on = sc.active;  // the same in every wave
+        beta = sc.beta;
+      }
+#pragma unroll
+      for (int q = 0; q < GB; ++q) {
+        const int row = r0 + W * q;
+        // p = z + beta p_old formed as k_dof1 stores it
+        if (row < NE) ush[row * 64 + lane] = gi[q] >= 0 ? (pcg ? fma(beta, v[q], z[q]) : v[q]) : 0.0;
+      }
+    }
+  }
+  // (an empty statement that uses them)
+  asm volatile("" ::"v"(warm[0]), "v"(warm[1]), "v"(warm[2]), "v"(warm[3]), "v"(warm[4]));
+  if (!on) return;
+  if (SPLIT) __syncthreads();
+  {  // rigid motion removed from the vertex rows
+    const double x0 = ush[lane], x1 = ush[64 + lane], th = ush[3 * 64 + lane] - x1;
+    if (SPLIT) __syncthreads();
+    for (int v = wave; v < 8; v += W) {
+      const int row = vertex_dof<P>(v);
+      ush[row * 64 + lane] = rigid_free<P>(ush[row * 64 + lane], row, x0, x1, th);
+    }
+    if (SPLIT) __syncthreads();
+  }
+  const cptr tab = scalar_table(t.kfac);
+  const double* __restrict__ Ec = E + cell;
+  const lds_vec u = (lds_vec)(ush + lane);
+  const int nch = fac_chains(t.d);
+  double* __restrict__ sl = s.slots + t.slot_off;
+  const int32_t* __restrict__ si_ = t.sidx + el;
+  if (!SPLIT) {
+    double acc[2][n][n], tot[2][n][n];
+    for (int ch = 0; ch < nch; ++ch) {
+      clear<P, 2>(acc);
+      factored_rows<P, n, 2>(t.d, tab, Ec, ch, nch, 0, u, acc);
+#pragma unroll
+      for (int a = 0; a < NE; ++a) {
+        double& v = tot[a & 1][(a >> 1) / n][(a >> 1) % n];
+        const double w = acc[a & 1][(a >> 1) / n][(a >> 1) % n];
+        v = ch == 0 ? w : v + w;
+      }
+    }
+    int si[NE];
+#pragma unroll
+    for (int r = 0; r < NE; ++r) si[r] = si_[(int64_t)r * t.npad];
+#pragma unroll
+    for (int r = 0; r < NE; ++r)
+      if (valid && si[r] >= 0) sl[si[r]] = tot[r & 1][(r >> 1) / n][(r >> 1) % n];
+    return;
+  }
+  // Partial results in LDS, [chain][CP n n][64]: both components at once
+  // (CP = 2) or, where that takes too much, one after the other.  slots: the
+  // scatter slots of the wave's rows a = wave, wave + W, ..., SB at a time.
+  constexpr int CP = P <= 2 ? 2 : 1, NR = CP * n * n, SB = (NR + 3) / 4;
+  int si[2][SB];
+  auto slots_of = [&](int h, int a0) {  // row a of phase h: component h (CP = 1) or a % 2 (CP = 2)
+#pragma unroll
+    for (int q = 0; q < SB; ++q) {
+      const int a = min(a0 + W * q, NR - 1);
+      si[h][q] = si_[(int64_t)(CP == 2 ? a : 2 * a + h) * t.npad];
+    }
+  };
+  auto put = [&](int ch, int c, const double (&a)[n][n]) {
+#pragma unroll
+    for (int q = 0; q < n * n; ++q) ush[(ch * NR + (CP == 2 ? 2 * q + c : q)) * 64 + lane] = a[q / n][q % n];
+  };
+  auto scatter = [&](int h) {
+    for (int a0 = wave; a0 < NR; a0 += W * SB) {
+      if (a0 != wave) slots_of(h, a0);
+#pragma unroll
+      for (int q = 0; q < SB; ++q) {
+        const int a = a0 + W * q;
+        if (a >= NR) break;  // uniform
+        double v = ush[a * 64 + lane];
+        for (int ch = 1; ch < nch; ++ch) v += ush[(ch * NR + a) * 64 + lane];
+        if (valid && si[h][q] >= 0) sl[si[h][q]] = v;
+      }
+    }
+  };
+  auto finish = [&](auto store) {  // store(h): this wave's part of phase h
+#pragma unroll
+    for (int h = 0; h < 2 / CP; ++h) slots_of(h, wave);
+#pragma unroll
+    for (int h = 0; h < 2 / CP; ++h) {
+      __syncthreads();  // the previous contents are no longer read
+      store(h);
+      __syncthreads();
+      scatter(h);
+    }
+  };
+  if (2 * nch <= W) {  // one component of one chain per wave
+    const int ch = wave >> 1, c = wave & 1;
+    double acc[1][n][n];
+    clear<P, 1>(acc);
+    if (ch < nch) factored_rows<P, n, 1>(t.d, tab, Ec, ch, nch, c, u, acc);
+    finish([&](int h) {
+      if (ch < nch && (CP == 2 || c == h)) put(ch, c, acc[0]);
+    });
+    return;
+  }
+  double acc[2][n][n];
+  clear<P, 2>(acc);
+  if (wave < nch) factored_rows<P, n, 2>(t.d, tab, Ec, wave, nch, 0, u, acc);
+  finish([&](int h) {
+    if (wave >= nch) return;
+    if (CP == 2) {
+      put(wave, 0, acc[0]);
+      put(wave, 1, acc[1]);
+    } else {
+      put(wave, h, acc[h]);
+    }
+  });
+}
+
+// Tiles of 64 columns from any group, PM the largest order among them: n_split split tiles, one per block, then n_whole
+// tiles of order <= 2, one per wave.  At most 256 registers: two waves per SIMD.
+template <int PM>
+__global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_factored(const FacTile* __restrict__ tiles, int n_split,
+                                                                    int n_whole, int xcd_run,
+                                                                    const double* __restrict__ E,
+                                                                    const double* __restrict__ xin, PcgDev s, int mode,
+                                                                    int it_k) {
+  extern __shared__ double lds[];
+  if ((int)blockIdx.x >= n_split) {
+    const int W = blockDim.x >> 6, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = xcd_tile(blockIdx.x - n_split, gridDim.x - n_split, xcd_run) * W + wave;
+    if (i >= n_whole) return;
+    const FacTile t = tiles[n_split + i];
+    double* mine = lds + wave * ne_of(PM < 2 ? PM : 2) * 64;  // waves of a block may hold different orders
+    if (t.p == 1) return factored_tile<1, false>(t, E, xin, s, mode, it_k, mine);
+    if constexpr (PM >= 2) factored_tile<2, false>(t, E, xin, s, mode, it_k, mine);
+    return;
+  }
+  const FacTile t = tiles[xcd_tile(blockIdx.x, n_split, xcd_run)];
+  if constexpr (PM >= 4)
+    if (t.p == 4) return factored_tile<4, true>(t, E, xin, s, mode, it_k, lds);
+  if constexpr (PM >= 3)
+    if (t.p == 3) return factored_tile<3, true>(t, E, xin, s, mode, it_k, lds);
+  if constexpr (PM >= 2)
+    if (t.p == 2) return factored_tile<2, true>(t, E, xin, s, mode, it_k, lds);
+  factored_tile<1, true>(t, E, xin, s, mode, it_k, lds);
+}
+
+}  // namespace
+
+void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run,
+                          const double* E, const double* xin, const PcgDev& s, int mode, int it_k, hipStream_t st,
+                          hipEvent_t ev0, hipEvent_t ev1) {
+  const int blocks = f.n_split + (f.n_whole + f.waves - 1) / f.waves;
+  if (blocks == 0) return;
+  const dim3 grid(blocks), block(64 * f.waves);
+  const FacTile* tl = tiles + f.tile_begin;
+  const uint32_t lds = (uint32_t)f.lds;
+  switch (f.p_max) {
+    case 1: launch_timed(k_elem_factored<1>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
+    case 2: launch_timed(k_elem_factored<2>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
+    case 3: launch_timed(k_elem_factored<3>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
+    default: launch_timed(k_elem_factored<4>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
+  }
+}
+
+}  // namespace mto

@@ -33,6 +33,14 @@ constexpr int frj_of(int p) { return mbm_of(p) * 64 + 4 * tr_of(p); }
 constexpr int asm_ntp_of(int p) { return (ne_of(p) * (ne_of(p) + 1) / 2 + 1) / 2 * 2; }
 constexpr int asm_cols_of(int p) { return p == 1 ? 32 : p == 2 ? 14 : p == 3 ? 8 : 4; }
 
+// Tables of the sum-factorised element product (factor_tables): doubles per
+// cell interval of the x factors (a and b packed, c full) and, per (cell
+// interval, input function l), of the y factors (8 columns of n = p + 1).
+constexpr int fac_x_of(int p) { return (p + 1) * (p + 2) + (p + 1) * (p + 1); }
+constexpr int fac_y_of(int p) { return 8 * (p + 1); }
+// Their length, padded to whole 1 KB copies.
+constexpr int fac_table_of(int p, int d) { return (d * (fac_x_of(p) + (p + 1) * fac_y_of(p)) + 127) / 128 * 128; }
+
 // Host-side K_s tables of Appendix B's composite integration:
 // ks[s*ne*ne + i*ne + j] for density cell s of a d x d grid.
 std::vector<double> subcell_tables(int p, int d, double nu);
@@ -58,6 +66,16 @@ std::vector<double> mfma_fragments(const std::vector<double>& ks, int p, int d);
 // step's 4 reduction indices, [kq][r] = K_s[16 mbm + r][4 jj + kq] (zero
 // beyond n_e).  Without a vector-ALU tail it equals mfma_fragments.
 std::vector<double> staged_fragments(const std::vector<double>& ks, int p, int d);
+
+// 1D integrals of the sum-factorised product over each of the d cell intervals
+// s of the unit interval, n = p + 1 functions: a(i,k) = int phi_i' phi_k',
+// b(i,k) = int phi_i phi_k, c(i,k) = int phi_i' phi_k.  First [d][fac_x_of(p)]:
+// a packed (upper triangle by rows), b packed, c [i][k]; then
+// [d][l = 0..p][8][j = 0..p], the y factors with the plane-stress constants
+// folded in: D11 b(j,l), D33 b(j,l), D33 a(j,l), D11 a(j,l), D12 c(l,j),
+// D33 c(l,j), D33 c(j,l), D12 c(j,l); zeros up to fac_table_of(p, d).  Long
+// double, rounded once.
+std::vector<double> factor_tables(int p, int d, double nu);
 
 // The columns of K_s at the element's 8 vertex DOFs (local DOFs 0..3 and
 // 2(p+1)..2(p+1)+3, k = 0..7 in that order) as MFMA A operands: for k-step jj

@@ -44,6 +44,7 @@ struct GroupDev {
   int32_t stored;          // products of this group read kst (k_elem_stored) instead of contracting K_s
   const double* kfragv;    // the vertex columns of K_s as A fragments [S][2][MB][64] (vertex_fragments)
   const double* ks;        // plain K_s [S][ne][ne]
+  const double* kfac;      // 1D tables of the sum-factorised product (factor_tables)
   const double* kdiag;     // diag(K_s) [S][ne]
   const double* kabs;      // row sums of |K_s| [S][ne] (l1 smoother)
   const int32_t* gidx;     // [NEP][npad] free DOF (instance-local) of local DOF, -1 absent
@@ -199,6 +200,38 @@ void launch_elem(const GroupDev& g, int path, const Tile* tiles, const double* E
 void launch_elem_fused(const GroupDev* groups, const Tile* tiles, int tile_begin, int n_tiles, int xcd_run,
                        size_t lds_bytes, const double* E, const double* xin, const PcgDev& s, int mode, int it_k,
                        hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
+// One launch of the sum-factorised product (mto_factor.hip): tiles of 64
+// columns from tile_begin on, n_split of them
+// split over the `waves` waves of a block, then n_whole taken one per wave;
+// p_max: the largest order among their groups.
+constexpr int FAC_MAX_W = 4;
+// Chains of the cell rows of a d x d grid (see mto_factor.hip): at most one
+// per wave, as even as that allows.
+__host__ __device__ constexpr int fac_chains(int d) {
+  return d <= 4 ? d : d == 5 ? 2 : d == 6 ? 3 : 4;
+}
+// A tile with its group's arrays at its first column: one descriptor load
+// before its data.
+struct FacTile {
+  const int32_t* gidx;   // [NEP][npad], [NE][npad], [npad] as in GroupDev
+  const int32_t* sidx;
+  const int32_t* cell;
+  const double* kfac;
+  int64_t dof_off, slot_off;
+  int32_t npad, count, sys, pc_begin, pc_end, p, d, pad;
+};
+struct FactoredLaunch {
+  int32_t tile_begin, n_split, n_whole, p_max, waves;
+  size_t lds;
+};
+inline size_t fac_lds_bytes(int p, int d, int waves, bool split) {
+  // partial results of both components at once for p <= 2, of one at a time above
+  const int ch = fac_chains(d) * (p <= 2 ? 2 : 1);
+  return 8 * (size_t)(split ? (ch > 2 ? ch : 2) * 32 : waves * 64) * ne_of(p);
+}
+void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run,
+                          const double* E, const double* xin, const PcgDev& s, int mode, int it_k, hipStream_t st,
+                          hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // K_e = sum_s E_s K_s of every column of the group, packed upper triangles
 // [npad][asm_ntp_of(p)] (stored element matrices)
 void launch_elem_assemble(const GroupDev& g, const double* E, double* kst, hipStream_t st);

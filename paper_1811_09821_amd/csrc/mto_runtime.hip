@@ -67,6 +67,9 @@ struct GroupHost {
   std::vector<int32_t> inst_begin;
   double* kfrag = nullptr;
   double* kfrags = nullptr;  // null without a vector-ALU tail (kfrag serves the LDS-staged kernel then)
+  // sum-factorised product (mto_set_tile ks = -3, the default): its 64-column tiles
+  int factored = 0, fac_tile_begin = 0, fac_n_tiles = 0;
+  double* kfac = nullptr;
   // stored element matrices (mto_set_tile ks = -2): K_e assembled per design, products read them
   int stored = 0;
   double* kst = nullptr;
@@ -186,6 +189,9 @@ struct mto_plan {
   bool fused = false;
   int fused_tile_begin = 0, fused_n_tiles = 0;
   size_t fused_lds = 0;
+  // the sum-factorised product of every group that uses it, in one launch (the head of the fused tiles)
+  FactoredLaunch fac{};
+  FacTile* d_fac_tiles = nullptr;
   GroupDev* d_groups_cur = nullptr;  // the groups' current device views (after the last rebuild_tiles)
   // element-block Schwarz smoother (MTO_PRECOND_MG_ASM)
   GroupDev* d_groups = nullptr;
@@ -256,6 +262,7 @@ struct mto_plan {
     o.kst = g.kst;
     o.stored = g.stored;
     o.kfragv = g.kfragv;
+    o.kfac = g.kfac;
     o.ks = g.ks;
     o.kdiag = g.kdiag;
     o.kabs = g.kabs;
@@ -296,6 +303,39 @@ void destroy_graphs(mto_plan* P) {
       *g = nullptr;
     }
   P->bound = false;
+}
+
+// Whether a tile of the group may go one to a wave: few enough rows of cells
+// and functions for one wave to be done with it about as fast as its gather.
+bool may_go_whole(const GroupHost& g) { return g.p <= 2 && g.d <= 5; }
+
+// The sum-factorised launch of groups gs (their tiles consecutive, in this
+// order, those that may go whole last).
+//   Up to 256 tiles (one per CU) every tile is split over four waves: the
+// launch ends with its slowest tile, and a split one ends sooner (200 x 100
+// mesh, 60 p = 4 tiles: 21 us; 31 over two waves, 46 in one).  Beyond that
+// the small tiles go whole: split, they would hold the blocks that the large
+// ones wait for (254 of the 314 tiles of that mesh: 21 against 42 us).
+//   More than 256 split tiles fill the chip by themselves and take one wave
+// per chain of cell rows, the least that keeps chains apart (400 x 200, 783
+// p = 4 tiles: 73 us; 82 with four waves).
+FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs) {
+  FactoredLaunch f{};
+  f.waves = 4;
+  int total = 0, n_chains = 0;
+  for (auto* g : gs) total += g->fac_n_tiles;
+  auto whole = [&](const GroupHost* g) { return total > 256 && may_go_whole(*g); };
+  for (auto* g : gs) {
+    if (g->fac_n_tiles == 0) continue;
+    if (f.n_split + f.n_whole == 0) f.tile_begin = g->fac_tile_begin;
+    (whole(g) ? f.n_whole : f.n_split) += g->fac_n_tiles;
+    if (!whole(g)) n_chains = std::max(n_chains, fac_chains(g->d));
+    f.p_max = std::max(f.p_max, g->p);
+  }
+  if (n_chains > 0 && f.n_split > 256) f.waves = n_chains;
+  for (auto* g : gs)
+    f.lds = std::max(f.lds, fac_lds_bytes(whole(g) ? std::min(f.p_max, 2) : g->p, g->d, f.waves, !whole(g)));
+  return f;
 }
 
 // Tiles for every group with its current ncol, then the tiles of the
@@ -347,18 +387,24 @@ int rebuild_tiles(mto_plan* P) {
     else
       g.ms_n_tiles = (int)P->tiles.size() - g.ms_tile_begin;
   }
-  // the combined tiles of the fused product: 64 columns, groups by decreasing work per column
+  // the combined tiles of the fused product: 64 columns, the groups of the sum-factorised product first,
+  // then by decreasing work per column
   {
     std::vector<int> order(P->groups.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
       const GroupHost &a = P->groups[x], &b = P->groups[y];
+      if (a.factored != b.factored) return a.factored > b.factored;
+      // the sum-factorised launches want the tiles that may go one to a wave last
+      if (a.factored && may_go_whole(a) != may_go_whole(b)) return may_go_whole(b);
       return (double)a.S * a.ne * a.ne > (double)b.S * b.ne * b.ne;
     });
     P->fused_tile_begin = (int)P->tiles.size();
     P->fused_lds = 0;
+    std::vector<FacTile> ft;  // the same tiles for the sum-factorised product
     for (int gi : order) {
-      const GroupHost& g = P->groups[gi];
+      GroupHost& g = P->groups[gi];
+      g.fac_tile_begin = (int)ft.size();
       P->fused_lds = std::max(P->fused_lds, elem_lds_staged_bytes(g.p, 1));
       for (int i = 0; i < P->n_inst; ++i) {
         const int a = g.inst_begin[i], b = g.inst_begin[i + 1];
@@ -378,10 +424,22 @@ int rebuild_tiles(mto_plan* P) {
             t.pc_begin = sd.chunk_begin;
             t.pc_end = sd.chunk_end;
             P->tiles.push_back(t);
+            ft.push_back(FacTile{g.gidx + e, g.sidx + e, g.cell + e, g.kfac, t.dof_off, t.slot_off, g.npad, t.count,
+                                 t.sys, t.pc_begin, t.pc_end, g.p, g.d, 0});
           }
         }
       }
+      g.fac_n_tiles = (int)ft.size() - g.fac_tile_begin;
     }
+    std::vector<const GroupHost*> gs;
+    for (int gi : order)
+      if (P->groups[gi].factored) gs.push_back(&P->groups[gi]);
+    P->fac = factored_launch(gs);
+    if (!P->d_fac_tiles) {  // 64 columns whatever the shapes: the count never changes
+      int rc = dev_alloc(P, &P->d_fac_tiles, ft.size());
+      if (rc) return rc;
+    }
+    if (!ft.empty()) HIP_TRY(hipMemcpy(P->d_fac_tiles, ft.data(), ft.size() * sizeof(FacTile), hipMemcpyHostToDevice));
     P->fused_n_tiles = (int)P->tiles.size() - P->fused_tile_begin;
   }
   if (P->tiles.size() > P->tiles_cap) {
@@ -459,8 +517,8 @@ bool read_tile_cache(const char* path, std::map<TileKey, TileChoice>& out) {
     TileKey k;
     TileChoice v;
     if (sscanf(line, "%63s %d %d %d %d %d %lf", arch, &k.p, &k.d, &k.size_class, &v.ncol, &v.ks, &v.us) != 7 ||
-        (v.ncol != 1 && v.ncol != 2 && v.ncol != 4) || v.ks < -2 || v.ks == -1 || v.ks > 8 || k.p < 0 ||
-        k.p > MTO_MAX_P || (v.ks == -2 && (k.p == 0 || v.ncol != 1)) ||
+        (v.ncol != 1 && v.ncol != 2 && v.ncol != 4) || v.ks < -3 || v.ks == -1 || v.ks > 8 || k.p < 0 ||
+        k.p > MTO_MAX_P || (v.ks < -1 && (k.p == 0 || v.ncol != 1)) ||
         k.d < 0 || k.d > MTO_MAX_D * MTO_MAX_P || (k.p > 0 && k.d < 1) || (k.p > 0 && k.d > MTO_MAX_D) ||
         (k.p > 0 && v.ks == 0 && (k.p < 3 || v.ncol == 4)) || (k.p == 0 && (v.ks != 0 || v.ncol == 4))) {
       ok = false;
@@ -478,7 +536,7 @@ bool write_tile_cache(const char* path, const std::map<TileKey, TileChoice>& c) 
   FILE* fh = fopen(tmp.c_str(), "w");
   if (!fh) return false;
   fprintf(fh, "# element-contraction tile shapes: arch p d size_class(log2 columns) ncol ks us_per_launch\n"
-              "# ks 0: LDS-staged tables, 64 ncol columns per tile; ks -2: stored element matrices\n"
+              "# ks 0: LDS-staged tables, 64 ncol columns per tile; ks -2: stored element matrices, ks -3: sum-factorised product\n"
               "# p 0: the plan's choice between one launch for all its d groups (ncol 1) and one per group (ncol 2)\n");
   for (auto& kv : c)
     fprintf(fh, "%s %d %d %d %d %d %.3f\n", kv.first.arch.c_str(), kv.first.p, kv.first.d, kv.first.size_class,
@@ -854,6 +912,7 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
     g.mb = mb_of(g.p);
     g.ncol = 1;
     g.waves = std::min(4, g.S);
+    g.factored = P->prm.kernel_path == MTO_PATH_MFMA;
   }
   // order groups by (p, d) for stable output
   for (int gi = 0; gi < (int)P->groups.size(); ++gi) {
@@ -911,7 +970,7 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
     if ((rc = dev_upload(P, &g.gidx, gidx)) || (rc = dev_upload(P, &g.sidx, sidx)) ||
         (rc = dev_upload(P, &g.msidx, msidx)) ||
         (rc = dev_upload(P, &g.cell, cell)) || (rc = dev_upload(P, &g.ks, ks)) || (rc = dev_upload(P, &g.kfrag, kfr)) ||
-        (rc = dev_upload(P, &g.kfragv, kfv)) ||
+        (rc = dev_upload(P, &g.kfragv, kfv)) || (rc = dev_upload(P, &g.kfac, factor_tables(g.p, g.d, P->prm.nu))) ||
         (valu_tail(g.p) && (rc = dev_upload(P, &g.kfrags, staged_fragments(ks, g.p, g.d)))) ||
         (rc = dev_upload(P, &g.kdiag, kdiag)) || (rc = dev_upload(P, &g.kabs, kabs)))
       return cleanup(rc);
@@ -1004,12 +1063,15 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
 
 // ---- enqueue helpers (all launches on st; usable under stream capture) ----
 
-// One group's product: its stored element matrices when it has them (they
-// hold this design's moduli once the set-up or mto_autotune assembled them),
-// else the contraction.
+// One group's product: the sum-factorised one, its stored element matrices
+// when it has them (they hold this design's moduli once the set-up or
+// mto_autotune assembled them), else the contraction.
 void enq_elem_group(mto_plan* P, const GroupHost& g, const double* xin, int mode, int it_k, hipStream_t st,
                     hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
-  if (g.stored && P->prm.kernel_path == MTO_PATH_MFMA)
+  if (g.factored) {
+    launch_elem_factored(P->d_fac_tiles, factored_launch({&g}), P->n_sys > 1 ? 8 : 0, P->E, xin, P->pcg(),
+                         mode, it_k, st, ev0, ev1);
+  } else if (g.stored && P->prm.kernel_path == MTO_PATH_MFMA)
     launch_elem_stored(P->gdev(g), P->d_tiles, xin, P->pcg(), mode, it_k, st, ev0, ev1);
   else
     launch_elem(P->gdev(g), P->prm.kernel_path, P->d_tiles, P->E, xin, P->pcg(), mode, it_k, st, ev0, ev1);
@@ -1022,6 +1084,7 @@ int ensure_stored(mto_plan* P, GroupHost& g) {
     if (rc) return rc;
   }
   g.stored = 1;
+  g.factored = 0;
   return MTO_OK;
 }
 
@@ -1038,7 +1101,9 @@ void enq_elem_all(mto_plan* P, const double* xin, int mode, int it_k, hipStream_
                       P->fused_lds, P->E, xin, s, mode, it_k, st);
     return;
   }
-  for (auto& g : P->groups) enq_elem_group(P, g, xin, mode, it_k, st);
+  launch_elem_factored(P->d_fac_tiles, P->fac, P->n_sys > 1 ? 8 : 0, P->E, xin, s, mode, it_k, st);
+  for (auto& g : P->groups)
+    if (!g.factored) enq_elem_group(P, g, xin, mode, it_k, st);
 }
 
 void enq_residual(mto_plan* P, hipStream_t st);
@@ -1608,7 +1673,9 @@ int mto_apply_stiffness_noalloc(mto_plan* P, const double* rho, const double* x,
   // slots that no element writes (missing neighbours) must read as zero; the
   // array keeps the previous call's contents
   launch_fill(slots, 0.0, P->n_slots_tot, st);
-  for (auto& g : P->groups) launch_elem(P->gdev(g), P->prm.kernel_path, P->d_tiles, E, q, s, ELEM_APPLY, 0, st);
+  launch_elem_factored(P->d_fac_tiles, P->fac, P->n_sys > 1 ? 8 : 0, E, q, s, ELEM_APPLY, 0, st);
+  for (auto& g : P->groups)
+    if (!g.factored) launch_elem(P->gdev(g), P->prm.kernel_path, P->d_tiles, E, q, s, ELEM_APPLY, 0, st);
   launch_fill(y, 0.0, P->n_u, st);
   launch_assemble_to_full(s, P->f2f, y, 0, st);
   return check_launch("apply_stiffness_noalloc");
@@ -1811,8 +1878,20 @@ int mto_set_tile(mto_plan* P, int32_t p, int32_t d, int32_t ncol, int32_t ks) {
     if (!any) return fail(MTO_EINVAL, "no group with this (p, d)");
     return rebuild_tiles(P);
   }
+  if (P && ks == -3) {  // the sum-factorised product for the group(s)
+    bool any = false;
+    for (auto& g : P->groups)
+      if (p <= 0 || (g.p == p && g.d == d)) {
+        if (P->prm.kernel_path == MTO_PATH_MFMA) g.factored = 1;
+        g.stored = 0;
+        any = true;
+      }
+    if (!any) return fail(MTO_EINVAL, "no group with this (p, d)");
+    P->fused = false;
+    return rebuild_tiles(P);
+  }
   if (!P || (ncol != 1 && ncol != 2 && ncol != 4) || ks < 0 || ks > 8)
-    return fail(MTO_EINVAL, "ncol must be 1, 2 or 4 and ks -2..8");
+    return fail(MTO_EINVAL, "ncol must be 1, 2 or 4 and ks -3..8");
   P->fused = false;
   if (ks == 0 && ncol == 4) return fail(MTO_EINVAL, "the LDS-staged contraction takes ncol 1 or 2");
   for (auto& g : P->groups)
@@ -1826,6 +1905,7 @@ int mto_set_tile(mto_plan* P, int32_t p, int32_t d, int32_t ncol, int32_t ks) {
           return fail(MTO_EINVAL, "tile shape exceeds the LDS limit");
         g.lds_nc = ncol;
         g.stored = 0;
+        g.factored = 0;
         continue;
       }
       const int k = std::min<int>(ks, g.S);
@@ -1834,6 +1914,7 @@ int mto_set_tile(mto_plan* P, int32_t p, int32_t d, int32_t ncol, int32_t ks) {
       g.waves = k;
       g.lds_nc = 0;
       g.stored = 0;
+      g.factored = 0;
     }
   return rebuild_tiles(P);
 }
@@ -1879,7 +1960,16 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
       continue;
     }
     g.stored = 0;
+    g.factored = 0;
     if (hit != cache.end() && hit->second.ks == -2) hit = cache.end();  // stored matrices not allowed: time shapes
+    if (hit != cache.end() && hit->second.ks == -3) {
+      g.factored = 1;
+      char line[200];
+      snprintf(line, sizeof line, "p=%d d=%d ncol=1 ks=-3: cached (sum-factorised; %s, %d columns class, %.3f us when tuned)\n",
+               g.p, g.d, arch.c_str(), key.size_class, hit->second.us);
+      rep += line;
+      continue;
+    }
     if (hit != cache.end() && hit->second.ks == 0 && g.p >= 3 &&
         elem_lds_staged_bytes(g.p, hit->second.ncol) <= ELEM_LDS_STAGED_LIMIT) {
       g.lds_nc = hit->second.ncol;
@@ -1933,6 +2023,29 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
           best_ks = ks;
         }
       }
+    {  // the sum-factorised product
+      g.factored = 1;
+      int rc = rebuild_tiles(P);
+      if (rc) return rc;
+      for (int w = 0; w < 3; ++w) enq_elem_group(P, g, P->q, ELEM_APPLY, 0, st);
+      const int reps = 20;
+      HIP_TRY(hipEventRecord(e0, st));
+      for (int w = 0; w < reps; ++w) enq_elem_group(P, g, P->q, ELEM_APPLY, 0, st);
+      HIP_TRY(hipEventRecord(e1, st));
+      HIP_TRY(hipEventSynchronize(e1));
+      float ms = 0.f;
+      HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+      const double tt = ms / reps;
+      char line[160];
+      snprintf(line, sizeof line, "p=%d d=%d ncol=1 ks=-3: %.3f us (sum-factorised)\n", g.p, g.d, 1e3 * tt);
+      rep += line;
+      g.factored = 0;
+      if (tt < best) {
+        best = tt;
+        best_nc = 1;
+        best_ks = -3;
+      }
+    }
     if (g.p >= 3 && P->prm.stored_matrices) {  // stored element matrices: assembled for these moduli, then timed
       int rc = ensure_stored(P, g);
       if (rc) return rc;
@@ -1959,6 +2072,7 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
       }
     }
     g.stored = best_ks == -2 ? 1 : 0;
+    g.factored = best_ks == -3 ? 1 : 0;
     g.lds_nc = best_ks == 0 ? best_nc : 0;
     g.ncol = best_ks <= 0 ? 1 : best_nc;
     g.waves = best_ks <= 0 ? 1 : best_ks;
@@ -2009,8 +2123,8 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
   }
   for (auto& g : P->groups) {
     char line[96];
-    if (g.stored)
-      snprintf(line, sizeof line, "p=%d d=%d ncol=1 ks=-2: chosen\n", g.p, g.d);
+    if (g.stored || g.factored)
+      snprintf(line, sizeof line, "p=%d d=%d ncol=1 ks=%d: chosen\n", g.p, g.d, g.factored ? -3 : -2);
     else
       snprintf(line, sizeof line, "p=%d d=%d ncol=%d ks=%d: chosen\n", g.p, g.d, g.lds_nc ? g.lds_nc : g.ncol,
                g.lds_nc ? 0 : g.waves);
@@ -2063,6 +2177,9 @@ int mto_time_contraction(mto_plan* P, const double* rho, int32_t reps, int32_t i
   std::vector<hipEvent_t> ev(2 * ng * (size_t)reps, nullptr);
   for (auto& e : ev) HIP_TRY(hipEventCreate(&e));
   const bool fused = P->fused && P->prm.kernel_path == MTO_PATH_MFMA;
+  int fac0 = -1;  // the group whose events time the sum-factorised launch
+  for (size_t gi = 0; gi < ng && fac0 < 0; ++gi)
+    if (P->groups[gi].factored) fac0 = (int)gi;
   for (int i = 0; i < reps; ++i) {
     const int k = i % G;
     if (fused) {
@@ -2073,7 +2190,11 @@ int mto_time_contraction(mto_plan* P, const double* rho, int32_t reps, int32_t i
       for (size_t gi = 0; gi < ng; ++gi) {
         auto& g = P->groups[gi];
         hipEvent_t* e = &ev[2 * (ng * i + gi)];
-        enq_elem_group(P, g, P->p, ELEM_PCG, k, st, e[0], e[1]);
+        if (!g.factored)
+          enq_elem_group(P, g, P->p, ELEM_PCG, k, st, e[0], e[1]);
+        else if ((int)gi == fac0)  // one launch for all of them
+          launch_elem_factored(P->d_fac_tiles, P->fac, P->n_sys > 1 ? 8 : 0, P->E, P->p, s, ELEM_PCG, k,
+                               st, e[0], e[1]);
       }
     }
     launch_dof1(s, k, st);
@@ -2085,7 +2206,8 @@ int mto_time_contraction(mto_plan* P, const double* rho, int32_t reps, int32_t i
   double total = 0.0;
   for (size_t j = 0; j < ng * (size_t)reps; ++j) {
     const GroupHost& gj = P->groups[j % ng];
-    if (fused ? (j % ng != 0 || P->fused_n_tiles == 0) : (gj.stored ? gj.ms_n_tiles : gj.n_tiles) == 0)
+    if (fused ? (j % ng != 0 || P->fused_n_tiles == 0)
+              : gj.factored ? (int)(j % ng) != fac0 : (gj.stored ? gj.ms_n_tiles : gj.n_tiles) == 0)
       continue;  // nothing launched, events never recorded
     float ms = 0.f;
     HIP_TRY(hipEventElapsedTime(&ms, ev[2 * j], ev[2 * j + 1]));

@@ -11,6 +11,7 @@
 // the cell: exact, since the integrand has degree <= 2p per direction.
 // Accumulation in long double, rounded once to double.
 
+#include <algorithm>
 #include <cmath>
 #include <utility>
 #include <vector>
@@ -117,6 +118,42 @@ std::vector<double> subcell_tables(int p, int d, double nu) {
   for (int s = 0; s < S; ++s)
     for (int i = 0; i < ne; ++i)
       for (int j = 0; j < i; ++j) out[(size_t)s * ne * ne + i * ne + j] = out[(size_t)s * ne * ne + j * ne + i];
+  return out;
+}
+
+std::vector<double> factor_tables(int p, int d, double nu) {
+  const int n = p + 1, X = fac_x_of(p), Y = fac_y_of(p);
+  std::vector<double> out((size_t)fac_table_of(p, d), 0.0);
+  const ld q = 1.0L / (1.0L - (ld)nu * nu), D11 = q, D12 = q * nu, D33 = q * (1 - (ld)nu) / 2;
+  ld gx[16], gw[16];
+  gauss_legendre(n, gx, gw);
+  for (int s = 0; s < d; ++s) {
+    std::vector<ld> a((size_t)n * n, 0), b(a), c(a);
+    for (int g = 0; g < n; ++g) {
+      const ld h = 2.0L / d, wt = gw[g] * h / 4;  // dx = dxi / 2
+      ld f[16], df[16];
+      shape_1d(p, -1 + h * s + h * (gx[g] + 1) / 2, f, df);
+      for (int i = 0; i < n; ++i)
+        for (int k = 0; k < n; ++k) {
+          a[i * n + k] += wt * (2 * df[i]) * (2 * df[k]);
+          b[i * n + k] += wt * f[i] * f[k];
+          c[i * n + k] += wt * (2 * df[i]) * f[k];
+        }
+    }
+    double* x = &out[(size_t)s * X];
+    for (const auto* m : {&a, &b})
+      for (int i = 0; i < n; ++i)
+        for (int k = i; k < n; ++k) *x++ = (double)(*m)[i * n + k];
+    for (int i = 0; i < n * n; ++i) *x++ = (double)c[i];
+    double* y = &out[(size_t)d * X + (size_t)s * n * Y];
+    for (int l = 0; l < n; ++l)
+      for (int j = 0; j < n; ++j) {
+        const int jl = std::min(j, l) * n + std::max(j, l);  // a and b symmetric to the last bit
+        const ld v[8] = {D11 * b[jl], D33 * b[jl], D33 * a[jl], D11 * a[jl],
+                         D12 * c[l * n + j], D33 * c[l * n + j], D33 * c[j * n + l], D12 * c[j * n + l]};
+        for (int k = 0; k < 8; ++k) y[(size_t)l * Y + k * n + j] = (double)v[k];
+      }
+  }
   return out;
 }
 
