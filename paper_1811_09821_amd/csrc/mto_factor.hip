@@ -164,7 +164,11 @@ __device__ __forceinline__ void clear(double (&acc)[NC][P + 1][P + 1]) {
 
 // One tile by the W waves of a block (SPLIT), or by one wave (W = 1, no
 // barrier); ush: its LDS, [NE][64] element vectors, then partial results.
-template <int P, bool SPLIT>
+// VERT: xin is nonzero at vertex DOFs only (read there alone) and the results
+// are added to the slots: with the slots holding K z from before the V-cycle's
+// coarse-grid correction, which changes z at vertex DOFs, this gives K z after
+// it at a third of a full product's multiply-adds (3.8 k at p = 4, d = 5).
+template <int P, bool SPLIT, bool VERT>
 __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __restrict__ E,
                                               const double* __restrict__ xin, const PcgDev& s, int mode, int it_k,
                                               double* ush) {
@@ -184,18 +188,19 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
   double warm[5];
 #pragma unroll
   for (int k = 0; k < 5; ++k) warm[k] = E[cell + min(16 * k, t.d * t.d - 1)];
-  // Rows wave, wave + W, ...: GB index loads, then their values, all
+  // Rows wave, wave + W, ... (VERT: the eight vertex rows): GB index loads, then their values, all
   // unconditional (clamped row; an absent DOF reads the system's first).
   // Every wave reduces the PCG scalars itself, while its first values load: no
   // barrier, and no memory round trip more than the values take.
   double beta = 0.0;
   bool on = true;
   {
-    constexpr int GB = SPLIT ? (NE + 3) / 4 : (NE + 1) / 2;
+    constexpr int NG = VERT ? 8 : NE, GB = SPLIT ? (NG + 3) / 4 : VERT ? 8 : (NE + 1) / 2;
+    auto row_of = [](int k) { return VERT ? vertex_dof<P>(k) : k; };
     int gi[GB];
-    for (int r0 = wave; r0 < NE; r0 += W * GB) {
+    for (int r0 = wave; r0 < NG; r0 += W * GB) {
 #pragma unroll
-      for (int q = 0; q < GB; ++q) gi[q] = gi_[(int64_t)min(r0 + W * q, NE - 1) * t.npad];
+      for (int q = 0; q < GB; ++q) gi[q] = gi_[(int64_t)row_of(min(r0 + W * q, NG - 1)) * t.npad];
       const int it = pcg && r0 == wave ? *s.it_base + it_k : 0;
       double v[GB], z[GB];
 #pragma unroll
@@ -211,9 +216,9 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
       }
 #pragma unroll
       for (int q = 0; q < GB; ++q) {
-        const int row = r0 + W * q;
+        const int k = r0 + W * q, row = row_of(k);
         // p = z + beta p_old formed as k_dof1 stores it
-        if (row < NE) ush[row * 64 + lane] = gi[q] >= 0 ? (pcg ? fma(beta, v[q], z[q]) : v[q]) : 0.0;
+        if (k < NG) ush[row * 64 + lane] = gi[q] >= 0 ? (pcg ? fma(beta, v[q], z[q]) : v[q]) : 0.0;
       }
     }
   }
@@ -230,6 +235,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
     }
     if (SPLIT) __syncthreads();
   }
+  constexpr int NK = VERT ? 2 : n;
   const cptr tab = scalar_table(t.kfac);
   const double* __restrict__ Ec = E + cell;
   const lds_vec u = (lds_vec)(ush + lane);
@@ -240,7 +246,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
     double acc[2][n][n], tot[2][n][n];
     for (int ch = 0; ch < nch; ++ch) {
       clear<P, 2>(acc);
-      factored_rows<P, n, 2>(t.d, tab, Ec, ch, nch, 0, u, acc);
+      factored_rows<P, NK, 2>(t.d, tab, Ec, ch, nch, 0, u, acc);
 #pragma unroll
       for (int a = 0; a < NE; ++a) {
         double& v = tot[a & 1][(a >> 1) / n][(a >> 1) % n];
@@ -251,9 +257,16 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
     int si[NE];
 #pragma unroll
     for (int r = 0; r < NE; ++r) si[r] = si_[(int64_t)r * t.npad];
+    double old[VERT ? NE : 1];
+    if (VERT) {
 #pragma unroll
-    for (int r = 0; r < NE; ++r)
-      if (valid && si[r] >= 0) sl[si[r]] = tot[r & 1][(r >> 1) / n][(r >> 1) % n];
+      for (int r = 0; r < NE; ++r) old[VERT ? r : 0] = sl[max(si[r], 0)];
+    }
+#pragma unroll
+    for (int r = 0; r < NE; ++r) {
+      const double v = tot[r & 1][(r >> 1) / n][(r >> 1) % n];
+      if (valid && si[r] >= 0) sl[si[r]] = VERT ? old[VERT ? r : 0] + v : v;
+    }
     return;
   }
   // Partial results in LDS, [chain][CP n n][64]: both components at once
@@ -261,11 +274,16 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
   // scatter slots of the wave's rows a = wave, wave + W, ..., SB at a time.
   constexpr int CP = P <= 2 ? 2 : 1, NR = CP * n * n, SB = (NR + 3) / 4;
   int si[2][SB];
+  double old[2][VERT ? SB : 1];
   auto slots_of = [&](int h, int a0) {  // row a of phase h: component h (CP = 1) or a % 2 (CP = 2)
 #pragma unroll
     for (int q = 0; q < SB; ++q) {
       const int a = min(a0 + W * q, NR - 1);
       si[h][q] = si_[(int64_t)(CP == 2 ? a : 2 * a + h) * t.npad];
+    }
+    if (VERT) {
+#pragma unroll
+      for (int q = 0; q < SB; ++q) old[h][VERT ? q : 0] = sl[max(si[h][q], 0)];
     }
   };
   auto put = [&](int ch, int c, const double (&a)[n][n]) {
@@ -281,7 +299,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
         if (a >= NR) break;  // uniform
         double v = ush[a * 64 + lane];
         for (int ch = 1; ch < nch; ++ch) v += ush[(ch * NR + a) * 64 + lane];
-        if (valid && si[h][q] >= 0) sl[si[h][q]] = v;
+        if (valid && si[h][q] >= 0) sl[si[h][q]] = VERT ? old[h][VERT ? q : 0] + v : v;
       }
     }
   };
@@ -300,7 +318,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
     const int ch = wave >> 1, c = wave & 1;
     double acc[1][n][n];
     clear<P, 1>(acc);
-    if (ch < nch) factored_rows<P, n, 1>(t.d, tab, Ec, ch, nch, c, u, acc);
+    if (ch < nch) factored_rows<P, NK, 1>(t.d, tab, Ec, ch, nch, c, u, acc);
     finish([&](int h) {
       if (ch < nch && (CP == 2 || c == h)) put(ch, c, acc[0]);
     });
@@ -308,7 +326,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
   }
   double acc[2][n][n];
   clear<P, 2>(acc);
-  if (wave < nch) factored_rows<P, n, 2>(t.d, tab, Ec, wave, nch, 0, u, acc);
+  if (wave < nch) factored_rows<P, NK, 2>(t.d, tab, Ec, wave, nch, 0, u, acc);
   finish([&](int h) {
     if (wave >= nch) return;
     if (CP == 2) {
@@ -322,7 +340,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
 
 // Tiles of 64 columns from any group, PM the largest order among them: n_split split tiles, one per block, then n_whole
 // tiles of order <= 2, one per wave.  At most 256 registers: two waves per SIMD.
-template <int PM>
+template <int PM, bool VERT>
 __global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_factored(const FacTile* __restrict__ tiles, int n_split,
                                                                     int n_whole, int xcd_run,
                                                                     const double* __restrict__ E,
@@ -335,36 +353,52 @@ __global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_factored(const FacTi
     if (i >= n_whole) return;
     const FacTile t = tiles[n_split + i];
     double* mine = lds + wave * ne_of(PM < 2 ? PM : 2) * 64;  // waves of a block may hold different orders
-    if (t.p == 1) return factored_tile<1, false>(t, E, xin, s, mode, it_k, mine);
-    if constexpr (PM >= 2) factored_tile<2, false>(t, E, xin, s, mode, it_k, mine);
+    if (t.p == 1) return factored_tile<1, false, VERT>(t, E, xin, s, mode, it_k, mine);
+    if constexpr (PM >= 2) factored_tile<2, false, VERT>(t, E, xin, s, mode, it_k, mine);
     return;
   }
   const FacTile t = tiles[xcd_tile(blockIdx.x, n_split, xcd_run)];
   if constexpr (PM >= 4)
-    if (t.p == 4) return factored_tile<4, true>(t, E, xin, s, mode, it_k, lds);
+    if (t.p == 4) return factored_tile<4, true, VERT>(t, E, xin, s, mode, it_k, lds);
   if constexpr (PM >= 3)
-    if (t.p == 3) return factored_tile<3, true>(t, E, xin, s, mode, it_k, lds);
+    if (t.p == 3) return factored_tile<3, true, VERT>(t, E, xin, s, mode, it_k, lds);
   if constexpr (PM >= 2)
-    if (t.p == 2) return factored_tile<2, true>(t, E, xin, s, mode, it_k, lds);
-  factored_tile<1, true>(t, E, xin, s, mode, it_k, lds);
+    if (t.p == 2) return factored_tile<2, true, VERT>(t, E, xin, s, mode, it_k, lds);
+  factored_tile<1, true, VERT>(t, E, xin, s, mode, it_k, lds);
 }
 
 }  // namespace
 
-void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run,
-                          const double* E, const double* xin, const PcgDev& s, int mode, int it_k, hipStream_t st,
-                          hipEvent_t ev0, hipEvent_t ev1) {
+namespace {
+template <bool VERT>
+void launch_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E, const double* xin,
+                     const PcgDev& s, int mode, int it_k, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
+  if (f.n_split + f.n_whole == 0) return;
   const int blocks = f.n_split + (f.n_whole + f.waves - 1) / f.waves;
-  if (blocks == 0) return;
   const dim3 grid(blocks), block(64 * f.waves);
   const FacTile* tl = tiles + f.tile_begin;
   const uint32_t lds = (uint32_t)f.lds;
+  auto go = [&](auto k) {
+    launch_timed(k, grid, block, lds, st, ev0, ev1, tl, (int)f.n_split, (int)f.n_whole, xcd_run, E, xin, s, mode, it_k);
+  };
   switch (f.p_max) {
-    case 1: launch_timed(k_elem_factored<1>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
-    case 2: launch_timed(k_elem_factored<2>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
-    case 3: launch_timed(k_elem_factored<3>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
-    default: launch_timed(k_elem_factored<4>, grid, block, lds, st, ev0, ev1, tl, f.n_split, f.n_whole, xcd_run, E, xin, s, mode, it_k); break;
+    case 1: go(k_elem_factored<1, VERT>); break;
+    case 2: go(k_elem_factored<2, VERT>); break;
+    case 3: go(k_elem_factored<3, VERT>); break;
+    default: go(k_elem_factored<4, VERT>); break;
   }
+}
+}  // namespace
+
+void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E,
+                          const double* xin, const PcgDev& s, int mode, int it_k, hipStream_t st, hipEvent_t ev0,
+                          hipEvent_t ev1) {
+  launch_factored<false>(tiles, f, xcd_run, E, xin, s, mode, it_k, st, ev0, ev1);
+}
+
+void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E,
+                            const double* dz, const PcgDev& s, hipStream_t st) {
+  launch_factored<true>(tiles, f, xcd_run, E, dz, s, ELEM_APPLY_RUNNING, 0, st, nullptr, nullptr);
 }
 
 }  // namespace mto

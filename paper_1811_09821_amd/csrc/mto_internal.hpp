@@ -77,12 +77,6 @@ std::vector<double> staged_fragments(const std::vector<double>& ks, int p, int d
 // double, rounded once.
 std::vector<double> factor_tables(int p, int d, double nu);
 
-// The columns of K_s at the element's 8 vertex DOFs (local DOFs 0..3 and
-// 2(p+1)..2(p+1)+3, k = 0..7 in that order) as MFMA A operands: for k-step jj
-// (k = 4 jj .. 4 jj + 3) and row block mb, lane l holds
-// K_s[mb*16 + l%16][vertex DOF 4 jj + l/16] (zero past n_e).  Length S*2*MB*64.
-std::vector<double> vertex_fragments(const std::vector<double>& ks, int p, int d);
-
 // One design instance after numbering.
 struct InstanceHost {
   int nelx = 0, nely = 0, L = 1;

@@ -589,74 +589,6 @@ __global__ __launch_bounds__(256) void k_elem_fused(const GroupDev* __restrict__
 }
 
 // ---------------------------------------------------------------------------
-// Vertex-column product: slots += sum_s E_s K_s[:, V] dz_V for a correction dz
-// that is nonzero only at vertex DOFs (V: the element's 8 vertex DOFs), which
-// is what the coarse-grid correction of the V-cycle adds to z.  With the
-// slots holding K z from before the correction this gives K z after it,
-// without the full product: the reduction runs over S * 8 instead of
-// S * NEP entries (two MFMA k-steps per cell, A = the vertex columns of K_s,
-// kfragv [S][2][MB][64]).  One wave per 16 element columns (blockIdx.y picks
-// the part of the tile); running systems only; dz's rigid motion removed as
-// in the other products.
-template <int P>
-__global__ __launch_bounds__(64) void k_elem_vertex(GroupDev g, const Tile* __restrict__ tiles,
-                                                   const double* __restrict__ E, const double* __restrict__ dz,
-                                                   PcgDev s) {
-  constexpr int NE = ne_of(P), MB = mb_of(P);
-  const Tile t = tiles[g.tile_begin + blockIdx.x];
-  const int c0 = blockIdx.y * 16;
-  if (c0 >= t.count || s.status[t.sys] != SYS_RUNNING) return;  // uniform over the wave
-  const int lane = threadIdx.x, n = lane & 15, kq = lane >> 4;
-  const bool valid = c0 + n < t.count;
-  const int el = t.elem_begin + c0 + (valid ? n : 0);
-  // dz at vertex DOFs kq and 4 + kq of this lane's column
-  double v[2];
-#pragma unroll
-  for (int jj = 0; jj < 2; ++jj) {
-    const int gi = valid ? g.gidx[vertex_dof<P>(4 * jj + kq) * g.npad + el] : -1;
-    const double x = dz[t.dof_off + (gi >= 0 ? gi : 0)];
-    v[jj] = gi >= 0 ? x : 0.0;
-  }
-  {  // rigid motion through DOFs 0, 1 (vertex (0,0)) and 3 (vertex (1,0) y): lanes n, 16 + n, 48 + n
-    const double x0 = __shfl(v[0], n), x1 = __shfl(v[0], 16 + n), th = __shfl(v[0], 48 + n) - x1;
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) v[jj] = rigid_free<P>(v[jj], vertex_dof<P>(4 * jj + kq), x0, x1, th);
-  }
-  int sidx[MB][4];
-  double old[MB][4];
-  double* __restrict__ sl = s.slots + t.slot_off;
-#pragma unroll
-  for (int b = 0; b < MB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = b * 16 + kq + 4 * r;
-      sidx[b][r] = (valid && row < NE) ? g.sidx[row * g.npad + el] : -1;
-      const double o = sl[sidx[b][r] >= 0 ? sidx[b][r] : 0];
-      old[b][r] = sidx[b][r] >= 0 ? o : 0.0;
-    }
-  const int cb = valid ? g.cell[el] : 0;
-  const double* __restrict__ kf = g.kfragv + lane;
-  d4 acc[MB];
-#pragma unroll
-  for (int b = 0; b < MB; ++b) acc[b] = d4{old[b][0], old[b][1], old[b][2], old[b][3]};
-  for (int sc = 0; sc < g.S; ++sc) {
-    const double e = valid ? E[cb + sc] : 0.0;
-#pragma unroll
-    for (int jj = 0; jj < 2; ++jj) {
-      const double bv = e * v[jj];
-#pragma unroll
-      for (int b = 0; b < MB; ++b)
-        acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(kf[(((size_t)sc * 2 + jj) * MB + b) * 64], bv, acc[b], 0, 0, 0);
-    }
-  }
-#pragma unroll
-  for (int b = 0; b < MB; ++b)
-#pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (sidx[b][r] >= 0) sl[sidx[b][r]] = acc[b][r];
-}
-
-// ---------------------------------------------------------------------------
 // Stored element matrices.  For a group whose contraction costs more than
 // reading its element matrix (p = 4, d = 5: 2 S n_e^2 = 125 kflop per column
 // against 10.2 KB per element, shared by the element's load cases; FP64 MFMA
@@ -1534,18 +1466,6 @@ void launch_elem_assemble(const GroupDev& g, const double* E, double* kst, hipSt
     case 2: hipLaunchKernelGGL(k_elem_assemble<2>, grid, block, 0, st, g, E, kst); break;
     case 3: hipLaunchKernelGGL(k_elem_assemble<3>, grid, block, 0, st, g, E, kst); break;
     default: hipLaunchKernelGGL(k_elem_assemble<4>, grid, block, 0, st, g, E, kst); break;
-  }
-}
-
-void launch_elem_vertex(const GroupDev& g, const Tile* tiles, const double* E, const double* dz, const PcgDev& s,
-                        hipStream_t st) {
-  if (g.n_tiles == 0) return;
-  const dim3 grid(g.n_tiles, g.ncol), block(64);
-  switch (g.p) {
-    case 1: hipLaunchKernelGGL(k_elem_vertex<1>, grid, block, 0, st, g, tiles, E, dz, s); break;
-    case 2: hipLaunchKernelGGL(k_elem_vertex<2>, grid, block, 0, st, g, tiles, E, dz, s); break;
-    case 3: hipLaunchKernelGGL(k_elem_vertex<3>, grid, block, 0, st, g, tiles, E, dz, s); break;
-    default: hipLaunchKernelGGL(k_elem_vertex<4>, grid, block, 0, st, g, tiles, E, dz, s); break;
   }
 }
 

@@ -42,7 +42,6 @@ struct GroupDev {
   const double* kfrags;    // the LDS-staged contraction's tables [S][NEP/4][frj_of(p)] (staged_fragments)
   const double* kst;       // stored element matrices K_e (stored != 0): [npad][asm_ntp_of(p)] packed upper triangles
   int32_t stored;          // products of this group read kst (k_elem_stored) instead of contracting K_s
-  const double* kfragv;    // the vertex columns of K_s as A fragments [S][2][MB][64] (vertex_fragments)
   const double* ks;        // plain K_s [S][ne][ne]
   const double* kfac;      // 1D tables of the sum-factorised product (factor_tables)
   const double* kdiag;     // diag(K_s) [S][ne]
@@ -240,9 +239,10 @@ void launch_elem_assemble(const GroupDev& g, const double* E, double* kst, hipSt
 void launch_elem_stored(const GroupDev& g, const Tile* tiles, const double* xin, const PcgDev& s, int mode, int it_k,
                         hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
 // slots += K[:, vertex DOFs] dz for the running systems (dz in the free-DOF
-// layout, read at vertex DOFs only; the slots hold K z before the call)
-void launch_elem_vertex(const GroupDev& g, const Tile* tiles, const double* E, const double* dz, const PcgDev& s,
-                        hipStream_t st);
+// layout, read at vertex DOFs only; the slots hold K z before the call), by
+// sum factorisation over the tiles of every group
+void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E,
+                            const double* dz, const PcgDev& s, hipStream_t st);
 // g = -E' lam_e^T K_s u_e per system, u from x and lam from y (free-DOF
 // layout of the systems; y = x gives the compliance sensitivity)
 void launch_sens(const GroupDev& g, const Tile* tiles, const double* dE, const double* x, const double* y,

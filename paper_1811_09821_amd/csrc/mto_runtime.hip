@@ -73,7 +73,6 @@ struct GroupHost {
   // stored element matrices (mto_set_tile ks = -2): K_e assembled per design, products read them
   int stored = 0;
   double* kst = nullptr;
-  double* kfragv = nullptr;
   double* ks = nullptr;
   double* kdiag = nullptr;
   double* kabs = nullptr;
@@ -189,9 +188,11 @@ struct mto_plan {
   bool fused = false;
   int fused_tile_begin = 0, fused_n_tiles = 0;
   size_t fused_lds = 0;
-  // the sum-factorised product of every group that uses it, in one launch (the head of the fused tiles)
+  // the sum-factorised product of every group that uses it, in one launch
   FactoredLaunch fac{};
+  FactoredLaunch fac_all{};  // the vertex update, over every group whatever its product
   FacTile* d_fac_tiles = nullptr;
+  size_t fac_tiles_cap = 0;
   GroupDev* d_groups_cur = nullptr;  // the groups' current device views (after the last rebuild_tiles)
   // element-block Schwarz smoother (MTO_PRECOND_MG_ASM)
   GroupDev* d_groups = nullptr;
@@ -261,7 +262,6 @@ struct mto_plan {
     o.kfrags = g.kfrags ? g.kfrags : g.kfrag;
     o.kst = g.kst;
     o.stored = g.stored;
-    o.kfragv = g.kfragv;
     o.kfac = g.kfac;
     o.ks = g.ks;
     o.kdiag = g.kdiag;
@@ -387,24 +387,18 @@ int rebuild_tiles(mto_plan* P) {
     else
       g.ms_n_tiles = (int)P->tiles.size() - g.ms_tile_begin;
   }
-  // the combined tiles of the fused product: 64 columns, the groups of the sum-factorised product first,
-  // then by decreasing work per column
+  // the combined tiles of the fused product: 64 columns, groups by decreasing work per column
   {
     std::vector<int> order(P->groups.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
       const GroupHost &a = P->groups[x], &b = P->groups[y];
-      if (a.factored != b.factored) return a.factored > b.factored;
-      // the sum-factorised launches want the tiles that may go one to a wave last
-      if (a.factored && may_go_whole(a) != may_go_whole(b)) return may_go_whole(b);
       return (double)a.S * a.ne * a.ne > (double)b.S * b.ne * b.ne;
     });
     P->fused_tile_begin = (int)P->tiles.size();
     P->fused_lds = 0;
-    std::vector<FacTile> ft;  // the same tiles for the sum-factorised product
     for (int gi : order) {
-      GroupHost& g = P->groups[gi];
-      g.fac_tile_begin = (int)ft.size();
+      const GroupHost& g = P->groups[gi];
       P->fused_lds = std::max(P->fused_lds, elem_lds_staged_bytes(g.p, 1));
       for (int i = 0; i < P->n_inst; ++i) {
         const int a = g.inst_begin[i], b = g.inst_begin[i + 1];
@@ -424,23 +418,52 @@ int rebuild_tiles(mto_plan* P) {
             t.pc_begin = sd.chunk_begin;
             t.pc_end = sd.chunk_end;
             P->tiles.push_back(t);
-            ft.push_back(FacTile{g.gidx + e, g.sidx + e, g.cell + e, g.kfac, t.dof_off, t.slot_off, g.npad, t.count,
-                                 t.sys, t.pc_begin, t.pc_end, g.p, g.d, 0});
           }
         }
       }
-      g.fac_n_tiles = (int)ft.size() - g.fac_tile_begin;
     }
-    std::vector<const GroupHost*> gs;
+    P->fused_n_tiles = (int)P->tiles.size() - P->fused_tile_begin;
+  }
+  if (P->prm.kernel_path == MTO_PATH_MFMA) {
+    // the same 64-column tiles for the sum-factorised product and vertex update (its descriptors carry
+    // the group's arrays): the tiles that may go one to a wave last, the rest by decreasing work
+    std::vector<int> order(P->groups.size());
+    for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
+    std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
+      const GroupHost &a = P->groups[x], &b = P->groups[y];
+      if (may_go_whole(a) != may_go_whole(b)) return may_go_whole(b);
+      return (double)a.d * a.ne * a.ne > (double)b.d * b.ne * b.ne;
+    });
+    std::vector<FacTile> ft;
+    auto tiles_of = [&](const std::vector<int>& groups) {
+      std::vector<const GroupHost*> gs;
+      for (int gi : groups) {
+        GroupHost& g = P->groups[gi];
+        g.fac_tile_begin = (int)ft.size();
+        for (int i = 0; i < P->n_inst; ++i)
+          for (int l = 0; l < P->L[i]; ++l) {
+            const int sysi = (int)P->c_off[i] + l;  // systems are numbered instance-major, like c
+            const SysDesc& sd = P->sys[sysi];
+            for (int e = g.inst_begin[i]; e < g.inst_begin[i + 1]; e += 64)
+              ft.push_back(FacTile{g.gidx + e, g.sidx + e, g.cell + e, g.kfac, sd.dof_off, sd.slot_off, g.npad,
+                                   std::min(64, g.inst_begin[i + 1] - e), sysi, sd.chunk_begin, sd.chunk_end, g.p, g.d, 0});
+          }
+        g.fac_n_tiles = (int)ft.size() - g.fac_tile_begin;
+        gs.push_back(&g);
+      }
+      return factored_launch(gs);
+    };
+    P->fac_all = tiles_of(order);
+    std::vector<int> sub;
     for (int gi : order)
-      if (P->groups[gi].factored) gs.push_back(&P->groups[gi]);
-    P->fac = factored_launch(gs);
-    if (!P->d_fac_tiles) {  // 64 columns whatever the shapes: the count never changes
-      int rc = dev_alloc(P, &P->d_fac_tiles, ft.size());
+      if (P->groups[gi].factored) sub.push_back(gi);
+    P->fac = sub.size() == order.size() ? P->fac_all : tiles_of(sub);
+    if (ft.size() > P->fac_tiles_cap) {  // at most twice the tiles of all groups
+      int rc = dev_alloc(P, &P->d_fac_tiles, 2 * (size_t)(P->fac_all.n_split + P->fac_all.n_whole));
       if (rc) return rc;
+      P->fac_tiles_cap = 2 * (size_t)(P->fac_all.n_split + P->fac_all.n_whole);
     }
     if (!ft.empty()) HIP_TRY(hipMemcpy(P->d_fac_tiles, ft.data(), ft.size() * sizeof(FacTile), hipMemcpyHostToDevice));
-    P->fused_n_tiles = (int)P->tiles.size() - P->fused_tile_begin;
   }
   if (P->tiles.size() > P->tiles_cap) {
     if (P->d_tiles) {
@@ -948,7 +971,6 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
     }
     std::vector<double> ks = subcell_tables(g.p, g.d, P->prm.nu);
     std::vector<double> kfr = mfma_fragments(ks, g.p, g.d);
-    std::vector<double> kfv = vertex_fragments(ks, g.p, g.d);
     std::vector<double> kdiag((size_t)g.S * g.ne), kabs((size_t)g.S * g.ne, 0.0);
     for (int s = 0; s < g.S; ++s)
       for (int j = 0; j < g.ne; ++j) {
@@ -970,7 +992,7 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
     if ((rc = dev_upload(P, &g.gidx, gidx)) || (rc = dev_upload(P, &g.sidx, sidx)) ||
         (rc = dev_upload(P, &g.msidx, msidx)) ||
         (rc = dev_upload(P, &g.cell, cell)) || (rc = dev_upload(P, &g.ks, ks)) || (rc = dev_upload(P, &g.kfrag, kfr)) ||
-        (rc = dev_upload(P, &g.kfragv, kfv)) || (rc = dev_upload(P, &g.kfac, factor_tables(g.p, g.d, P->prm.nu))) ||
+        (rc = dev_upload(P, &g.kfac, factor_tables(g.p, g.d, P->prm.nu))) ||
         (valu_tail(g.p) && (rc = dev_upload(P, &g.kfrags, staged_fragments(ks, g.p, g.d)))) ||
         (rc = dev_upload(P, &g.kdiag, kdiag)) || (rc = dev_upload(P, &g.kabs, kabs)))
       return cleanup(rc);
@@ -1158,7 +1180,7 @@ void enq_vertex_update(mto_plan* P, hipStream_t st) {
     enq_elem_all(P, P->z, ELEM_APPLY_RUNNING, 0, st);
     return;
   }
-  for (auto& g : P->groups) launch_elem_vertex(P->gdev(g), P->d_tiles, P->E, P->q, s, st);
+  launch_vertex_factored(P->d_fac_tiles, P->fac_all, P->n_sys > 1 ? 8 : 0, P->E, P->q, s, st);
 }
 
 // z = M r: one V-cycle.  Level-0 smoothing is Jacobi-type (z = D0^-1 r is
