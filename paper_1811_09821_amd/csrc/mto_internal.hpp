@@ -26,12 +26,22 @@ constexpr int tr_of(int p) { return valu_tail(p) ? ne_of(p) % 16 : 0; }         
 // Doubles per k-step of the LDS-staged contraction's tables (staged_fragments).
 constexpr int frj_of(int p) { return mbm_of(p) * 64 + 4 * tr_of(p); }
 
-// Element-block Schwarz smoother: the packed upper triangle of an element's
-// block inverse, padded to an even count (so every element's triangle starts
-// on 16 bytes), and the element columns per block of its application
-// (NE rows each, at most 256 threads, the blocks' triangles staged in LDS).
+// Stored element matrices: the packed upper triangle of a symmetric n_e x n_e
+// matrix, padded to an even count (so every element's triangle starts on 16
+// bytes), and the element columns per block of their product (NE rows each,
+// at most 256 threads, the triangles staged in LDS).
 constexpr int asm_ntp_of(int p) { return (ne_of(p) * (ne_of(p) + 1) / 2 + 1) / 2 * 2; }
 constexpr int asm_cols_of(int p) { return p == 1 ? 32 : p == 2 ? 14 : p == 3 ? 8 : 4; }
+
+// Element-block Schwarz smoother: the block inverses by tiles of
+// asm_elems_of(p) element columns, one wave each.  With G = p + 1, a column
+// takes G^2 lanes and its n_e = 2 G^2 rows form 2 G blocks of G; lane (i, j)
+// holds the entries (G A + i, G B + j) of the block pairs A <= B (a diagonal
+// pair in full).  Pair k is at [k / 2][lane][k % 2] of the tile's
+// asm_tile_of(p) doubles (8-15 % more than the packed triangle).
+constexpr int asm_elems_of(int p) { return 64 / ((p + 1) * (p + 1)); }
+constexpr int asm_lanes_of(int p) { return asm_elems_of(p) * (p + 1) * (p + 1); }
+constexpr int asm_tile_of(int p) { return ((p + 1) * (2 * p + 3) + 1) / 2 * 2 * asm_lanes_of(p); }
 
 // Tables of the sum-factorised element product (factor_tables): doubles per
 // cell interval of the x factors (a and b packed, c full) and, per (cell
@@ -120,8 +130,8 @@ struct Tile {
   int32_t sys;
   int32_t elem_begin;
   int32_t count;
-  int32_t pc_begin;   // the system's chunk (partial-sum) range; in the tiles of the Schwarz
-  int32_t pc_end;     //   application (GroupDev::ms_*) pc_begin is the instance's number of systems
+  int32_t pc_begin;   // the system's chunk (partial-sum) range; in the tiles of the stored-matrix
+  int32_t pc_end;     //   product (GroupDev::ms_*) pc_begin is the instance's number of systems
 };
 
 // A chunk of the free DOFs of one system for the vector kernels, with the

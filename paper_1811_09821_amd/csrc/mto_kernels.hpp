@@ -37,7 +37,7 @@ struct GroupDev {
   int32_t lds_tile_begin;  //   tiles of 64 lds_nc columns [lds_tile_begin, + lds_n_tiles)
   int32_t lds_n_tiles;
   int32_t ms_tile_begin;   // tiles of the first system of every instance (asm_cols_of(p) columns), on
-  int32_t ms_n_tiles;      //   which the Schwarz application serves all systems of the instance
+  int32_t ms_n_tiles;      //   which the stored-matrix product serves all systems of the instance
   const double* kfrag;     // MFMA A fragments [S*NEP/4][MB][64]
   const double* kfrags;    // the LDS-staged contraction's tables [S][NEP/4][frj_of(p)] (staged_fragments)
   const double* kst;       // stored element matrices K_e (stored != 0): [npad][asm_ntp_of(p)] packed upper triangles
@@ -48,8 +48,6 @@ struct GroupDev {
   const double* kabs;      // row sums of |K_s| [S][ne] (l1 smoother)
   const int32_t* gidx;     // [NEP][npad] free DOF (instance-local) of local DOF, -1 absent
   const int32_t* sidx;     // [MB*16][npad] slot (instance-local), -1 absent
-  const int32_t* msidx;    // [npad][ne][2]: (free DOF, slot) of local DOF a of column col at 2 (col ne + a),
-                           //   -1 absent: the Schwarz application's gathers, one contiguous run per tile
   const int32_t* cell;     // [npad] first density cell (global)
 };
 
@@ -334,16 +332,28 @@ void launch_mg_post0(const PcgDev& s, int it_k, int init, hipStream_t st);
 // ---- element-block additive Schwarz smoother (mto_mg.hip) ----
 // Per element column of group `gi`: the assembled operator restricted to the
 // element's free DOFs (own sum_s E_s K_s plus the shared-DOF entries of the
-// eight neighbours), inverted; binv holds its upper triangle packed by rows,
-// element-major: [npad][asm_ntp_of(p)] (the last entry of an odd count is
-// padding), zero rows/columns at absent or supported DOFs.  groups: device array of all group views;
-// nbr [8][npad]: global element index of each neighbour (-1: none);
-// el_group / el_col: group and column of every global element.
+// eight neighbours), inverted, into the tiles of binv (asm_tile_of; apos: each
+// column's position), zero rows/columns at absent or supported DOFs.  groups:
+// device array of all group views; nbr [8][npad]: global element index of
+// each neighbour (-1: none); el_group / el_col: group and column of every
+// global element.
 void launch_asm_block(const GroupDev& g, int gi, const GroupDev* groups, const int32_t* nbr, const int32_t* el_group,
-                      const int32_t* el_col, const double* E, double* binv, hipStream_t st);
-// slots2 = omega * B_e v_e for the running systems of the group's tiles,
-// with v_e gathered from v, or (resid) from v - assembled slots
-void launch_asm_apply(const GroupDev& g, const Tile* tiles, const double* binv, const double* v, int resid,
+                      const int32_t* el_col, const double* E, const int32_t* apos, double* binv, hipStream_t st);
+// A tile of the Schwarz application: up to asm_elems_of(p) element columns of
+// one instance, their block inverses, their (free DOF, slot) pairs (-1
+// absent, [column][n_e]) and the instance's systems sys .. sys + nsys - 1,
+// n_free DOFs and n_slots slots apart.
+struct AsmTile {
+  const double* m;
+  const int32_t* idx;
+  int64_t dof_off, slot_off, n_slots;  // of the first system
+  int32_t n_free, nfv, nfe;
+  int32_t count, sys, nsys, p, pad;
+};
+// slots2 = omega * B_e v_e for the running systems of the tiles (any group;
+// p_max: their largest order), v_e gathered from v, or (resid) from v -
+// assembled slots
+void launch_asm_apply(const AsmTile* tiles, int n_tiles, int p_max, int xcd_run, const double* v, int resid,
                       const PcgDev& s, double* slots2, double omega, hipStream_t st);
 // z = assembled slots2 (running systems)
 void launch_asm_z(const PcgDev& s, const double* slots2, hipStream_t st);

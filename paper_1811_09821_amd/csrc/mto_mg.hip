@@ -18,7 +18,6 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <cstdlib>
 #include <type_traits>
 
 #include "mto_kernels.hpp"
@@ -955,10 +954,20 @@ namespace {
 template <int P>
 constexpr int asm_block_threads() { return P == 1 ? 64 : P == 2 ? 128 : 256; }
 
-// Position of (a, b), a <= b, in the row-packed upper triangle of an NE x NE matrix.
-template <int NE>
-__device__ __forceinline__ int packed_index(int a, int b) {
-  return a * NE - (a * (a - 1)) / 2 + (b - a);
+// Layout of the element blocks (asm_* constants): the column at position
+// `pos` (tile pos / E, place pos % E), and within it the entry (a, b) of block
+// row a / G <= block column b / G.
+template <int P, typename T>
+__device__ __forceinline__ T* asm_column(T* binv, int pos) {
+  constexpr int E = asm_elems_of(P), G2 = (P + 1) * (P + 1);
+  const int tile = pos / E;
+  return binv + (int64_t)tile * asm_tile_of(P) + (pos - tile * E) * G2 * 2;
+}
+template <int P>
+__device__ __forceinline__ int asm_entry(int a, int b) {
+  constexpr int G = P + 1, NB = 2 * G, LN = asm_lanes_of(P);
+  const int A = a / G, B = b / G, k = A * NB - A * (A - 1) / 2 + (B - A);
+  return ((k >> 1) * LN + (a - A * G) * G + (b - B * G)) * 2 + (k & 1);
 }
 }
 
@@ -967,7 +976,8 @@ __global__ __launch_bounds__(asm_block_threads<P>()) void k_asm_block(const Grou
                                                          const int32_t* __restrict__ nbr,
                                                          const int32_t* __restrict__ el_group,
                                                          const int32_t* __restrict__ el_col,
-                                                         const double* __restrict__ E, double* __restrict__ binv) {
+                                                         const double* __restrict__ E,
+                                                         const int32_t* __restrict__ apos, double* __restrict__ binv) {
   constexpr int NE = ne_of(P), ASM_BLOCK = asm_block_threads<P>();
   constexpr int NEMAX = ne_of(MTO_MAX_P);
   __shared__ double A[NE][NE + 1];
@@ -1107,20 +1117,21 @@ __global__ __launch_bounds__(asm_block_threads<P>()) void k_asm_block(const Grou
   for (int a = tid; a < NE; a += ASM_BLOCK)
     if (!(A[a][a] > 0.0)) gid[a] = -1;
   __syncthreads();
-  // upper triangle, packed by rows (the assembled block is symmetric: both
+  // in the layout of the application (the assembled block is symmetric: both
   // triangles are the same sums in the same order)
+  double* __restrict__ bp = asm_column<P>(binv, apos[k]);
   for (int idx = tid; idx < NE * NE; idx += ASM_BLOCK) {
     const int a = idx / NE, b = idx - a * NE;
-    if (b < a) continue;
+    if (a / (P + 1) > b / (P + 1)) continue;
     const double v = (gid[a] < 0 || gid[b] < 0) ? (a == b ? -1.0 : 0.0) : A[a][b];
-    binv[(int64_t)k * asm_ntp_of(P) + packed_index<NE>(a, b)] = v;
+    bp[asm_entry<P>(a, b)] = v;
   }
 }
 
 // In-place inverse of the element blocks by blocked Gauss-Jordan elimination
 // on the matrix cores, one wave per element column: binv holds on entry the
-// packed upper triangle written by k_asm_block (a marked DOF: diagonal -1,
-// zero row) and on exit that of omega-free B_e, zero at marked DOFs.
+// block written by k_asm_block (a marked DOF: diagonal -1, zero row) and on
+// exit omega-free B_e, zero at marked DOFs.
 //   The block, symmetrically scaled to unit diagonal (marked and padding DOFs:
 //   identity rows), sits in MB x MB accumulator tiles of
 //   v_mfma_f64_16x16x4f64 (tile (bi, bj), register r: row 16 bi + l/16 + 4 r,
@@ -1136,12 +1147,12 @@ __global__ __launch_bounds__(asm_block_threads<P>()) void k_asm_block(const Grou
 //   every tile, the new pivot columns -C P^-1; the pivot rows become R and
 //   the pivot block P^-1.
 template <int P>
-__global__ __launch_bounds__(64, 2) void k_asm_invert(double* __restrict__ binv) {
-  constexpr int NE = ne_of(P), NTP = asm_ntp_of(P), MB = mb_of(P), NB = (NE + 3) / 4;
+__global__ __launch_bounds__(64, 2) void k_asm_invert(const int32_t* __restrict__ apos, double* __restrict__ binv) {
+  constexpr int NE = ne_of(P), MB = mb_of(P), NB = (NE + 3) / 4;
   __shared__ double dg[16 * MB];
   const int lane = threadIdx.x, lr = lane >> 4, lc = lane & 15;
-  double* __restrict__ bp = binv + (int64_t)blockIdx.x * NTP;
-  auto pk = [](int a, int b) { return a <= b ? packed_index<NE>(a, b) : packed_index<NE>(b, a); };
+  double* __restrict__ bp = asm_column<P>(binv, apos[blockIdx.x]);
+  auto pk = [](int a, int b) { return a <= b ? asm_entry<P>(a, b) : asm_entry<P>(b, a); };
   d4m acc[MB][MB];
 #pragma unroll
   for (int bi = 0; bi < MB; ++bi)
@@ -1239,7 +1250,7 @@ __global__ __launch_bounds__(64, 2) void k_asm_invert(double* __restrict__ binv)
 #pragma unroll
     for (int bj = 0; bj < MB; ++bj) acc[bk][bj][rk] = RB[bj];
   }
-  // unscale; upper triangle, packed by rows
+  // unscale; a diagonal block's two triangles take the same (upper) values
 #pragma unroll
   for (int bi = 0; bi < MB; ++bi)
 #pragma unroll
@@ -1247,207 +1258,193 @@ __global__ __launch_bounds__(64, 2) void k_asm_invert(double* __restrict__ binv)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int a = 16 * bi + lr + 4 * r, b = 16 * bj + lc;
-        if (a <= b && b < NE) bp[packed_index<NE>(a, b)] = acc[bi][bj][r] * dg[a] * dg[b];
+        if (a <= b && b < NE) {
+          const double v = acc[bi][bj][r] * dg[a] * dg[b];
+          bp[asm_entry<P>(a, b)] = v;
+          if (a / (P + 1) == b / (P + 1)) bp[asm_entry<P>(b, a)] = v;
+        }
       }
 }
 
-// slots2 = omega * B_e v_e.  A persistent grid (as many blocks of 256
-// threads as fit on the chip at once) walks the tiles of EB = asm_cols_of(P)
-// element columns of each instance's first system; block b takes the tiles
-// b, b + G, b + 2G, ... (G blocks) whose instance still has a running system,
-// found by all its threads at once and listed in LDS.  Thread (column c,
-// row a) serves the first NE EB threads.  A tile's packed triangles are one
-// contiguous range of binv, read with 16-byte loads by all threads and staged
-// in LDS, where each entry serves rows a and b; row a then sums B(a, b) v_b in
-// order of b.  The loads are software-pipelined: while a tile is computed
-// from LDS, the next tile's triangles and element vectors and the tile after
-// it's gather indices are in flight in registers, so HBM stays busy through
-// the LDS-bound sums.  Up to ASM_SYS systems of the instance per pass: the
-// element blocks are shared by its load cases, so one read of a block serves
-// all of them (an instance with more systems takes further passes, whose
-// element vectors are gathered in place).
+// slots2 = omega * B_e v_e for the running systems of every element's
+// instance, one wave per tile of asm_elems_of(P) elements, all groups in one
+// launch.
+//   HBM-bound by the blocks, so each symmetric entry is read once and serves
+// both of its rows.  An element's NE = 2 G^2 rows (G = P + 1) form 2 G blocks
+// of G; G^2 lanes take an element, lane (i, j) holding the entries (G A + i,
+// G B + j), A <= B, in registers: every load of a wave is one contiguous run
+// of 16 bytes per lane, all of a tile's loads are in flight at once, and
+// nothing is staged.  A lane adds e v_b to its row sums and e v_a to its column
+// sums; the G partial sums of a row and of its column meet in LDS.  Up to
+// ASM_SYS systems of the instance share one read of the blocks.
+//   A wave of p = 4 holds 110 VGPRs of entries in flight, so two waves per SIMD
+// cover the loads and the gathers of v.  Measured (us, v = r / v = the residual
+// with its slot gather), before -> after; before, a launch per group staged
+// packed triangles through LDS behind two barriers per tile (36 KB of LDS
+// traffic per p = 4 element against 10 KB here), four launches on the first two:
+//   61 x 33 mesh, p = 1..4, two systems: 19-24 in all -> 7.4
+//   400 x 200 mesh, p = 1..4, three systems: 114 in all -> 81 / 122
+//   16 designs, p = 4 in the main, two systems: 245 on average -> 205
+//   160 x 80 mesh, p = 3, one system: 17.3 -> 13.2
+// (2.3-3.7 TB/s over the blocks; three waves per SIMD with the entries taken in
+// two parts spilled and lost.)  A launch of at least ASM_PERSIST blocks takes a
+// bounded grid: late in a batch most systems have stopped, and one look at 64
+// tiles costs less than 64 waves that start and end.
 constexpr int ASM_SYS = 4;
-constexpr int ASM_THREADS = 256;
-constexpr int ASM_PERSIST_MIN = 4;
+constexpr int ASM_WAVES = 4;      // waves per block
+constexpr int ASM_YS = 65;        // row stride of the partial sums in LDS
+constexpr int ASM_GRID = 1024;    // blocks of a persistent launch
+constexpr int ASM_PERSIST = 4096;  // ... for launches of at least this many
+
+// LDS doubles of a wave: the tile's element vectors, then the partial sums
+__host__ __device__ constexpr int asm_lds_of(int p) { return 128 + 4 * (p + 1) * ASM_YS; }
+
+// orders this wave's LDS accesses (each wave uses its own part)
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// bit l: system l0 + l of the tile's instance runs (l < ASM_SYS)
+__device__ __forceinline__ uint64_t running_mask(const AsmTile& t, int l0, const PcgDev& s) {
+  const int lane = threadIdx.x & 63, l = l0 + min(lane, ASM_SYS - 1);
+  const int st = s.status[t.sys + min(l, t.nsys - 1)];
+  return __ballot(lane < ASM_SYS && l < t.nsys && st == SYS_RUNNING);
+}
 
 template <int P>
-__global__ __launch_bounds__(ASM_THREADS, 3) void k_asm_apply(GroupDev g, const Tile* __restrict__ tiles,
-                                                           const double* __restrict__ binv,
-                                                           const double* __restrict__ v, PcgDev s,
-                                                           double* __restrict__ out_slots, double omega, int resid) {
-  constexpr int NE = ne_of(P), NTP = asm_ntp_of(P), EB = asm_cols_of(P);
-  static_assert(NE * EB <= ASM_THREADS, "one thread per row and column");
-  constexpr int NB2 = EB * NTP / 2;                          // 16-byte words of a tile's triangles
-  constexpr int LPT = (NB2 + ASM_THREADS - 1) / ASM_THREADS;  // of those, per thread
-  constexpr int NW = ASM_THREADS / 64;
-  __shared__ double2 bs2[NB2];
-  __shared__ double vs[ASM_SYS][EB][NE];
-  __shared__ int list[ASM_THREADS];
-  __shared__ int wcount[NW];
-  const double* bs = (const double*)bs2;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c = tid / NE, a = tid - c * NE;
-  const int64_t n = g.ms_n_tiles;
-  const Tile* __restrict__ tl = tiles + g.ms_tile_begin;  // nsys of the tile's instance in pc_begin
-
-  auto running = [&](const Tile& t) {
-    bool any = false;
-    for (int l = 0; l < t.pc_begin; ++l) any |= s.status[t.sys + l] == SYS_RUNNING;
-    return any;
-  };
-  // gather indices of this thread's row of a tile (-1: no row, or a supported DOF)
-  auto indices = [&](const Tile& t, int& id, int& si) {
-    id = si = -1;
-    if (c < EB && c < t.count) {  // thread tid of the tile's contiguous run
-      const int2 q = ((const int2*)g.msidx)[(int64_t)t.elem_begin * NE + tid];
-      id = q.x;
-      si = q.y;
-    }
-  };
-  // a tile's triangles (words of absent columns of a partial last tile are not read)
-  auto triangles = [&](const Tile& t, double2 (&stg)[LPT]) {
-    const double2* __restrict__ src = (const double2*)(binv + (int64_t)t.elem_begin * NTP);
-    const int nw = t.count * (NTP / 2);
+__device__ __forceinline__ void asm_tile(const AsmTile& t, unsigned run, const double* __restrict__ v,
+                                         const PcgDev& s, double* __restrict__ out_slots, double omega, int resid,
+                                         double* lds) {
+  constexpr int G = P + 1, G2 = G * G, NE = 2 * G2, NB = 2 * G, NK = NB * (NB + 1) / 2;
+  constexpr int E = asm_elems_of(P), LN = asm_lanes_of(P), K2 = (NK + 1) / 2;
+  constexpr int RQ = (E * NE + 63) / 64;  // rows per lane
+  static_assert(E * NE <= 128 && RQ <= 2, "two rows per lane");
+  const int lane = threadIdx.x & 63;
+  const int lc = min(lane, LN - 1);  // idle lanes repeat the last one
+  const int e = lc / G2, i = (lc - e * G2) / G, j = lc - e * G2 - i * G;
+  double* vs = lds;
+  double* ys = lds + 128;
+  int2 id[RQ];
 #pragma unroll
-    for (int k = 0; k < LPT; ++k) {
-      const int i = tid + ASM_THREADS * k;
-      stg[k] = i < nw ? src[i] : double2{0.0, 0.0};
-    }
-  };
-  // element-vector entries of systems l0 .. l0 + ASM_SYS - 1 of a tile's
-  // instance (zero for a stopped system or no DOF); bit l of run: system l0 + l runs
-  auto gather = [&](const Tile& t, int l0, int id, double (&x)[ASM_SYS], unsigned& run) {
-    const int np = min(ASM_SYS, t.pc_begin - l0);
-    run = 0;
+  for (int q = 0; q < RQ; ++q) id[q] = ((const int2*)t.idx)[min(lane + 64 * q, t.count * NE - 1)];
+  double2 m[K2];
+  {
+    const double2* __restrict__ src = (const double2*)t.m + lc;
+#pragma unroll
+    for (int k = 0; k < K2; ++k) m[k] = src[k * LN];
+  }
+#pragma unroll
+  for (int q = 0; q < RQ; ++q)
+    if (lane + 64 * q >= t.count * NE) id[q] = int2{-1, -1};
+#pragma unroll 1
+  for (int l0 = 0; l0 < t.nsys; l0 += ASM_SYS) {
+    double x[RQ][ASM_SYS];
+    int lp = l0;  // opaque: as a function of the loop counter, every address below would be kept in registers
+    asm volatile("" : "+s"(lp));
 #pragma unroll
     for (int l = 0; l < ASM_SYS; ++l) {
-      x[l] = 0.0;
-      if (l >= np) continue;
-      const int sys = t.sys + l0 + l;
-      if (s.status[sys] != SYS_RUNNING) continue;  // the same address in every lane: one load
-      run |= 1u << l;
-      if (id >= 0) {
-        const SysDesc& sd = s.sys[sys];
-        const double* __restrict__ vsys = v + sd.dof_off;
-        x[l] = resid ? vsys[id] - slot_sum(s.slots + sd.slot_off, id, sd.nfv, sd.nfe) : vsys[id];
+      if (!((run >> l) & 1u)) continue;  // uniform
+      const double* __restrict__ vl = v + t.dof_off + (int64_t)(lp + l) * t.n_free;
+      const double* __restrict__ sl = s.slots + t.slot_off + (lp + l) * t.n_slots;
+#pragma unroll
+      for (int q = 0; q < RQ; ++q) {
+        const int ic = max(id[q].x, 0);
+        const double xv = vl[ic];
+        x[q][l] = resid ? xv - slot_sum(sl, ic, t.nfv, t.nfe) : xv;
       }
     }
-  };
-  // rows of one pass from LDS; slots2 of the running systems
-  const int ra = a * NE - (a * (a - 1)) / 2 - a;  // row a: entry (min, max) at cb + a (b < a) or ra + b
-  auto rows = [&](const Tile& t, int l0, int si, unsigned run) {
-    const int np = min(ASM_SYS, t.pc_begin - l0);
-    if (!(c < EB && c < t.count)) return;
-    const double* __restrict__ brow = bs + c * NTP;
-    double acc[ASM_SYS] = {0.0, 0.0, 0.0, 0.0};
-    const double* __restrict__ vc = &vs[0][c][0];
-    auto sum = [&](auto nl) {
-      constexpr int NL = decltype(nl)::value;
-#pragma unroll 5
-      for (int b = 0; b < NE; ++b) {
-        const int cb = b * NE - (b * (b - 1)) / 2 - b;
-        const double e = brow[b < a ? cb + a : ra + b];
 #pragma unroll
-        for (int l = 0; l < NL; ++l) acc[l] = fma(e, vc[l * EB * NE + b], acc[l]);
+    for (int l = 0; l < ASM_SYS; ++l) {
+      if (!((run >> l) & 1u)) continue;  // uniform
+#pragma unroll
+      for (int q = 0; q < RQ; ++q) vs[lane + 64 * q] = id[q].x >= 0 ? x[q][l] : 0.0;
+      wave_lds_sync();
+      double vc[NB], yc[NB];
+#pragma unroll
+      for (int B = 0; B < NB; ++B) {
+        vc[B] = vs[e * NE + B * G + j];
+        yc[B] = 0.0;
       }
-    };
-    switch (np) {  // uniform over the block
-      case 1: sum(std::integral_constant<int, 1>{}); break;
-      case 2: sum(std::integral_constant<int, 2>{}); break;
-      case 3: sum(std::integral_constant<int, 3>{}); break;
-      default: sum(std::integral_constant<int, 4>{}); break;
-    }
-    if (si < 0) return;
 #pragma unroll
-    for (int l = 0; l < ASM_SYS; ++l)
-      if ((run >> l) & 1u) out_slots[s.sys[t.sys + l0 + l].slot_off + si] = omega * acc[l];
-  };
-  auto put_vectors = [&](const Tile& t, const double (&x)[ASM_SYS]) {
-    if (!(c < EB)) return;
+      for (int A = 0; A < NB; ++A) {
+        const double vr = vs[e * NE + A * G + i];
+        double yr = 0.0;
 #pragma unroll
-    for (int l = 0; l < ASM_SYS; ++l) vs[l][c][a] = x[l];
-  };
-
-  // tiles at(0), ..., at(cnt - 1) (uniform tile indices): tile i is summed
-  // from LDS while tile i + 1's data and tile i + 2's indices load
-  auto pipeline = [&](int cnt, auto at) {
-    Tile tn = tl[at(0)];
-    double2 stg[LPT];
-    int id, si, id2 = -1, si2 = -1;
-    double x[ASM_SYS];
-    unsigned run;
-    triangles(tn, stg);
-    indices(tn, id, si);
-    Tile tn2 = tn;
-    if (cnt > 1) {
-      tn2 = tl[at(1)];
-      indices(tn2, id2, si2);
-    }
-    gather(tn, 0, id, x, run);
-    for (int i = 0; i < cnt; ++i) {
-      const Tile t = tn;
-      const int cur_id = id, cur_si = si;
-      const unsigned cur_run = run;
-      __syncthreads();  // the previous tile's sums have finished with bs2 and vs
-#pragma unroll
-      for (int k = 0; k < LPT; ++k) {
-        const int j = tid + ASM_THREADS * k;
-        if (j < NB2) bs2[j] = stg[k];
-      }
-      put_vectors(t, x);
-      if (i + 1 < cnt) {
-        tn = tn2;
-        id = id2;
-        si = si2;
-        triangles(tn, stg);
-        if (i + 2 < cnt) {
-          tn2 = tl[at(i + 2)];
-          indices(tn2, id2, si2);
+        for (int B = A; B < NB; ++B) {
+          const int k = A * NB - A * (A - 1) / 2 + (B - A);
+          const double b = k & 1 ? m[k >> 1].y : m[k >> 1].x;
+          yr = fma(b, vc[B], yr);
+          if (B > A) yc[B] = fma(b, vr, yc[B]);  // a diagonal block holds both triangles
         }
+        ys[A * ASM_YS + lane] = yr;
       }
-      __syncthreads();  // the tile's triangles and element vectors are in LDS
-      rows(t, 0, cur_si, cur_run);
-      if (i + 1 < cnt) gather(tn, 0, id, x, run);
-      for (int l0 = ASM_SYS; l0 < t.pc_begin; l0 += ASM_SYS) {  // instances with more systems
-        double xx[ASM_SYS];
-        unsigned rr;
-        gather(t, l0, cur_id, xx, rr);
-        __syncthreads();  // vs is free again
-        put_vectors(t, xx);
-        __syncthreads();
-        rows(t, l0, cur_si, rr);
+#pragma unroll
+      for (int B = 1; B < NB; ++B) ys[(NB + B) * ASM_YS + lane] = yc[B];
+      wave_lds_sync();
+      double* __restrict__ so = out_slots + t.slot_off + (lp + l) * t.n_slots;
+#pragma unroll
+      for (int q = 0; q < RQ; ++q) {
+        const int r = min(lane + 64 * q, E * NE - 1), er = r / NE, a = r - er * NE, A = a / G, ai = a - A * G;
+        const double* yp = ys + A * ASM_YS + er * G2;
+        double y = 0.0;
+#pragma unroll
+        for (int k = 0; k < G; ++k) y += yp[ai * G + k];
+        if (A > 0) {
+#pragma unroll
+          for (int k = 0; k < G; ++k) y += yp[NB * ASM_YS + k * G + ai];
+        }
+        if (id[q].y >= 0) so[id[q].y] = omega * y;
       }
+      wave_lds_sync();  // vs and ys are rewritten
     }
-  };
+    run = (unsigned)running_mask(t, l0 + ASM_SYS, s);
+  }
+}
 
-  if (gridDim.x >= n) {  // one tile per block (small launches): no list
-    if (blockIdx.x >= n) return;  // uniform over the block
-    const int ti = xcd_tile(blockIdx.x, (int)n, g.xcd_run);
-    if (!running(tl[ti])) return;
-    pipeline(1, [&](int) { return ti; });
+template <int PM>
+__global__ __launch_bounds__(64 * ASM_WAVES, 2) void k_asm_apply(const AsmTile* __restrict__ tiles, int n_tiles,
+                                                                int xcd_run, const double* __restrict__ v, PcgDev s,
+                                                                double* __restrict__ out_slots, double omega,
+                                                                int resid) {
+  __shared__ double lds[ASM_WAVES * asm_lds_of(PM)];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  double* mine = lds + wave * asm_lds_of(PM);
+  const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;  // blocks of one tile per wave
+  auto tile_at = [&](int64_t vb) { return vb < nb ? xcd_tile((int)vb, nb, xcd_run) * ASM_WAVES + wave : n_tiles; };
+  auto running = [&](const AsmTile& t) {
+    bool any = false;
+    for (int l = 0; l < t.nsys; ++l) any |= s.status[t.sys + l] == SYS_RUNNING;
+    return any;
+  };
+  auto run_tile = [&](const AsmTile& t) {
+    const unsigned run = (unsigned)running_mask(t, 0, s);
+    if (run == 0 && t.nsys <= ASM_SYS) return;
+    if constexpr (PM >= 4)
+      if (t.p == 4) return asm_tile<4>(t, run, v, s, out_slots, omega, resid, mine);
+    if constexpr (PM >= 3)
+      if (t.p == 3) return asm_tile<3>(t, run, v, s, out_slots, omega, resid, mine);
+    if constexpr (PM >= 2)
+      if (t.p == 2) return asm_tile<2>(t, run, v, s, out_slots, omega, resid, mine);
+    asm_tile<1>(t, run, v, s, out_slots, omega, resid, mine);
+  };
+  if ((int)gridDim.x == nb) {
+    const int ti = tile_at(blockIdx.x);
+    if (ti >= n_tiles) return;
+    run_tile(tiles[ti]);
     return;
   }
-  for (int64_t w0 = blockIdx.x; w0 < n; w0 += (int64_t)gridDim.x * ASM_THREADS) {
-    // this block's tiles w0 + k G, k = 0 .. 255, that still have work: listed in order
-    __syncthreads();  // list and wcount of the previous window are no longer read
-    // candidate w0 + tid G runs on this block's XCD (G is a multiple of 8);
-    // xcd_tile maps it to a tile so that each XCD takes neighbouring tiles
-    const int64_t vi = w0 + (int64_t)tid * gridDim.x;
-    const int ti = vi < n ? xcd_tile((int)vi, (int)n, g.xcd_run) : 0;
-    const bool on = vi < n && running(tl[ti]);
-    const uint64_t bal = __ballot(on);
-    if (lane == 0) wcount[wave] = __popcll(bal);
-    __syncthreads();
-    int off = 0, cnt = 0;
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-      off += w < wave ? wcount[w] : 0;
-      cnt += wcount[w];
+  // a bounded grid: each wave looks at 64 of its tiles at once and takes those
+  // with a running system, so that late in a batch the stopped ones cost little
+  for (int64_t b0 = blockIdx.x; b0 < nb; b0 += 64 * (int64_t)gridDim.x) {
+    const int ti = tile_at(b0 + lane * (int64_t)gridDim.x);
+    uint64_t on = __ballot(ti < n_tiles && running(tiles[min(ti, n_tiles - 1)]));
+    while (on) {
+      const int k = __builtin_ctzll(on);
+      on &= on - 1;
+      const AsmTile t = tiles[__builtin_amdgcn_readlane(ti, k)];
+      run_tile(t);
     }
-    if (on) list[off + __popcll(bal & ((1ull << lane) - 1ull))] = ti;
-    __syncthreads();
-    if (cnt == 0) continue;  // uniform over the block
-    pipeline(cnt, [&](int i) { return __builtin_amdgcn_readfirstlane(list[i]); });
   }
 }
 
@@ -1541,68 +1538,33 @@ void launch_mg_post0(const PcgDev& s, int it_k, int init, hipStream_t st) {
 }
 
 void launch_asm_block(const GroupDev& g, int gi, const GroupDev* groups, const int32_t* nbr, const int32_t* el_group,
-                      const int32_t* el_col, const double* E, double* binv, hipStream_t st) {
+                      const int32_t* el_col, const double* E, const int32_t* apos, double* binv, hipStream_t st) {
   if (g.n_elems == 0) return;
   const dim3 grid(g.n_elems);
+  auto go = [&](auto pc) {
+    constexpr int P = decltype(pc)::value;
+    hipLaunchKernelGGL(k_asm_block<P>, grid, dim3(asm_block_threads<P>()), 0, st, groups, gi, nbr, el_group, el_col, E,
+                       apos, binv);
+    hipLaunchKernelGGL(k_asm_invert<P>, grid, dim3(64), 0, st, apos, binv);
+  };
   switch (g.p) {
-    case 1: hipLaunchKernelGGL(k_asm_block<1>, grid, dim3(asm_block_threads<1>()), 0, st, groups, gi, nbr, el_group, el_col, E, binv); break;
-    case 2: hipLaunchKernelGGL(k_asm_block<2>, grid, dim3(asm_block_threads<2>()), 0, st, groups, gi, nbr, el_group, el_col, E, binv); break;
-    case 3: hipLaunchKernelGGL(k_asm_block<3>, grid, dim3(asm_block_threads<3>()), 0, st, groups, gi, nbr, el_group, el_col, E, binv); break;
-    default: hipLaunchKernelGGL(k_asm_block<4>, grid, dim3(asm_block_threads<4>()), 0, st, groups, gi, nbr, el_group, el_col, E, binv); break;
+    case 1: go(std::integral_constant<int, 1>{}); break;
+    case 2: go(std::integral_constant<int, 2>{}); break;
+    case 3: go(std::integral_constant<int, 3>{}); break;
+    default: go(std::integral_constant<int, 4>{}); break;
   }
-  switch (g.p) {
-    case 1: hipLaunchKernelGGL(k_asm_invert<1>, grid, dim3(64), 0, st, binv); break;
-    case 2: hipLaunchKernelGGL(k_asm_invert<2>, grid, dim3(64), 0, st, binv); break;
-    case 3: hipLaunchKernelGGL(k_asm_invert<3>, grid, dim3(64), 0, st, binv); break;
-    default: hipLaunchKernelGGL(k_asm_invert<4>, grid, dim3(64), 0, st, binv); break;
-  }
-}
-// Blocks of k_asm_apply<p> resident on the current device at once (cached per
-// device and order).
-static int asm_apply_blocks(int p) {
-  static int cache[64][4];
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) dev = 0;
-  int& nb = cache[dev][p - 1];
-  if (nb > 0) return nb;
-  int per_cu = 0, cus = 0;
-  hipError_t e;
-  switch (p) {
-    case 1: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_asm_apply<1>, ASM_THREADS, 0); break;
-    case 2: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_asm_apply<2>, ASM_THREADS, 0); break;
-    case 3: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_asm_apply<3>, ASM_THREADS, 0); break;
-    default: e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_asm_apply<4>, ASM_THREADS, 0); break;
-  }
-  if (e != hipSuccess || per_cu < 1) per_cu = 1;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1) cus = 256;
-  nb = per_cu * cus;
-  return nb;
 }
 
-void launch_asm_apply(const GroupDev& g, const Tile* tiles, const double* binv, const double* v, int resid,
+void launch_asm_apply(const AsmTile* tiles, int n_tiles, int p_max, int xcd_run, const double* v, int resid,
                       const PcgDev& s, double* slots2, double omega, hipStream_t st) {
-  if (g.ms_n_tiles == 0) return;
-  // persistent: the blocks that fit on the device at once, at most one per
-  // tile.  MTO_ASM_GRID (a positive integer) caps the count: the results do
-  // not depend on it (every tile is summed the same way by whichever block
-  // takes it), which lets tests run the pipeline and the tile windows of a
-  // large grid on small meshes.
-  // Launches of fewer than ASM_PERSIST_MIN tiles per resident block take one
-  // block per tile instead (the walk's list costs more than it saves there).
-  int nb = asm_apply_blocks(g.p);
-  if (g.ms_n_tiles < ASM_PERSIST_MIN * nb) nb = g.ms_n_tiles;
-  // a multiple of 8 blocks, so that block b and its candidates b + k G share XCD b mod 8
-  nb = (std::min(g.ms_n_tiles, nb) + 7) / 8 * 8;
-  if (const char* cap = std::getenv("MTO_ASM_GRID")) {
-    const int c = std::atoi(cap);
-    if (c > 0) nb = std::min(nb, c);
-  }
-  const dim3 grid(nb), block(ASM_THREADS);
-  switch (g.p) {
-    case 1: hipLaunchKernelGGL(k_asm_apply<1>, grid, block, 0, st, g, tiles, binv, v, s, slots2, omega, resid); break;
-    case 2: hipLaunchKernelGGL(k_asm_apply<2>, grid, block, 0, st, g, tiles, binv, v, s, slots2, omega, resid); break;
-    case 3: hipLaunchKernelGGL(k_asm_apply<3>, grid, block, 0, st, g, tiles, binv, v, s, slots2, omega, resid); break;
-    default: hipLaunchKernelGGL(k_asm_apply<4>, grid, block, 0, st, g, tiles, binv, v, s, slots2, omega, resid); break;
+  if (n_tiles == 0) return;
+  const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;
+  const dim3 grid(nb >= ASM_PERSIST ? ASM_GRID : nb), block(64 * ASM_WAVES);
+  switch (p_max) {
+    case 1: hipLaunchKernelGGL(k_asm_apply<1>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
+    case 2: hipLaunchKernelGGL(k_asm_apply<2>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
+    case 3: hipLaunchKernelGGL(k_asm_apply<3>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
+    default: hipLaunchKernelGGL(k_asm_apply<4>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
   }
 }
 void launch_asm_z(const PcgDev& s, const double* slots2, hipStream_t st) {

@@ -84,8 +84,9 @@ struct GroupHost {
   double flops = 0.0;  // 2 S ne^2 per element column
   std::vector<double> kv;  // host copy of the vertex-block table
   int kv_off = 0;
-  // element-block Schwarz smoother: packed inverses [npad/16][ne (ne+1)/2][16], neighbours [8][npad]
+  // element-block Schwarz smoother: inverses in tiles, each column's position in them, neighbours [8][npad]
   double* binv = nullptr;
+  int32_t* apos = nullptr;
   int32_t* nbr = nullptr;
   // QR-error indicator (built at its first use): instance and element of every column,
   // packed order-(p+1) cell tables
@@ -197,6 +198,8 @@ struct mto_plan {
   // element-block Schwarz smoother (MTO_PRECOND_MG_ASM)
   GroupDev* d_groups = nullptr;
   int32_t *d_el_group = nullptr, *d_el_col = nullptr;
+  AsmTile* d_asm_tiles = nullptr;  // the tiles of its application, all groups
+  int asm_n_tiles = 0, asm_p_max = 1;
   double* slots2 = nullptr;  // the Schwarz products, assembled like the slots
   double asm_omega = 0.0;
   // QR-error indicator: per instance first system, load cases, output offset, elements
@@ -268,7 +271,6 @@ struct mto_plan {
     o.kabs = g.kabs;
     o.gidx = g.gidx;
     o.sidx = g.sidx;
-    o.msidx = g.msidx;
     o.cell = g.cell;
     return o;
   }
@@ -772,6 +774,7 @@ int build_asm(mto_plan* P, const std::vector<InstanceHost>& I) {
       el_col[base[i] + e] = next[g]++;  // group columns: instance order, then element order
     }
   std::vector<GroupDev> gd;
+  std::vector<AsmTile> at;
   int rc;
   for (size_t g = 0; g < P->groups.size(); ++g) {
     GroupHost& G = P->groups[g];
@@ -793,9 +796,32 @@ int build_asm(mto_plan* P, const std::vector<InstanceHost>& I) {
     }
     if ((int64_t)G.ne * (G.ne + 1) / 2 * G.npad >= ((int64_t)1 << 31))
       return fail(MTO_EINVAL, "Schwarz smoother: too many elements of one (p, d) group for 32-bit block offsets");
-    if ((rc = dev_upload(P, &G.nbr, nbr)) || (rc = dev_alloc(P, &G.binv, (size_t)asm_ntp_of(G.p) * G.npad))) return rc;
+    // tiles of asm_elems_of(p) columns, each instance's starting its own
+    const int E = asm_elems_of(G.p);
+    std::vector<int32_t> apos(G.npad, 0), tile0(n + 1, 0);
+    for (int i = 0; i < n; ++i) {
+      tile0[i + 1] = tile0[i] + (G.inst_begin[i + 1] - G.inst_begin[i] + E - 1) / E;
+      for (int k = G.inst_begin[i]; k < G.inst_begin[i + 1]; ++k) apos[k] = tile0[i] * E + (k - G.inst_begin[i]);
+    }
+    const size_t doubles = (size_t)asm_tile_of(G.p) * tile0[n];
+    if ((rc = dev_upload(P, &G.nbr, nbr)) || (rc = dev_upload(P, &G.apos, apos)) || (rc = dev_alloc(P, &G.binv, doubles)))
+      return rc;
+    launch_fill(G.binv, 0.0, (int64_t)doubles, 0);  // absent columns of a partial tile
+    for (int i = 0; i < n; ++i)
+      for (int t = tile0[i]; t < tile0[i + 1]; ++t) {
+        const int k0 = G.inst_begin[i] + (t - tile0[i]) * E;
+        const SysDesc& sd = P->sys[P->c_off[i]];  // the instance's first system; the others follow it
+        at.push_back(AsmTile{G.binv + (size_t)asm_tile_of(G.p) * t, G.msidx + 2 * (size_t)k0 * G.ne, sd.dof_off,
+                             sd.slot_off, I[i].n_slots, sd.n_free, sd.nfv, sd.nfe, std::min(E, G.inst_begin[i + 1] - k0),
+                             (int32_t)P->c_off[i], P->L[i], G.p, 0});
+      }
+    P->asm_p_max = std::max(P->asm_p_max, G.p);
     gd.push_back(P->gdev(G));
   }
+  // the tiles of the largest orders first
+  std::stable_sort(at.begin(), at.end(), [](const AsmTile& a, const AsmTile& b) { return a.p > b.p; });
+  P->asm_n_tiles = (int)at.size();
+  if ((rc = dev_upload(P, &P->d_asm_tiles, at))) return rc;
   if ((rc = dev_upload(P, &P->d_groups, gd)) || (rc = dev_upload(P, &P->d_el_group, el_group)) ||
       (rc = dev_upload(P, &P->d_el_col, el_col)) || (rc = dev_alloc(P, &P->slots2, P->n_slots_tot)))
     return rc;
@@ -1190,13 +1216,14 @@ void enq_vertex_update(mto_plan* P, hipStream_t st) {
 void enq_vcycle(mto_plan* P, int it_k, int init, hipStream_t st) {
   const PcgDev s = P->pcg();
   if (P->prm.precond == MTO_PRECOND_MG_ASM) {
-    for (auto& g : P->groups) launch_asm_apply(P->gdev(g), P->d_tiles, g.binv, P->r, 0, s, P->slots2, P->asm_omega, st);
+    const int run = P->n_sys > 1 ? 8 : 0;
+    launch_asm_apply(P->d_asm_tiles, P->asm_n_tiles, P->asm_p_max, run, P->r, 0, s, P->slots2, P->asm_omega, st);
     launch_asm_z(s, P->slots2, st);
     enq_elem_all(P, P->z, ELEM_APPLY_RUNNING, 0, st);
     enq_coarse_correction(P, st);
     enq_vertex_update(P, st);
     // post-smoothing: the residual r - A0 z is formed in the gather
-    for (auto& g : P->groups) launch_asm_apply(P->gdev(g), P->d_tiles, g.binv, P->r, 1, s, P->slots2, P->asm_omega, st);
+    launch_asm_apply(P->d_asm_tiles, P->asm_n_tiles, P->asm_p_max, run, P->r, 1, s, P->slots2, P->asm_omega, st);
     launch_asm_post(s, P->slots2, it_k, init, st);
     return;
   }
@@ -1238,7 +1265,7 @@ void enq_setup(mto_plan* P, const double* rho, const double* u0, hipStream_t st)
   if (P->prm.precond == MTO_PRECOND_MG_ASM)
     for (size_t gi = 0; gi < P->groups.size(); ++gi) {
       const GroupHost& g = P->groups[gi];
-      launch_asm_block(P->gdev(g), (int)gi, P->d_groups, g.nbr, P->d_el_group, P->d_el_col, P->E, g.binv, st);
+      launch_asm_block(P->gdev(g), (int)gi, P->d_groups, g.nbr, P->d_el_group, P->d_el_col, P->E, g.apos, g.binv, st);
     }
   // PCG iterates on the correction x (from 0); the solution is xs_hi + xs_lo
   launch_fill(P->x, 0.0, P->n_vec, st);
