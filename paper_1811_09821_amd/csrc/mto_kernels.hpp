@@ -288,8 +288,9 @@ void launch_qr(const QrGroupDev& g, const double* E, const double* x, const SysD
                hipStream_t st);
 // Refinement indicators (see mto_adapt.hip): Gamma^a per (system, element)
 // from displacements x in the free-DOF layout; Gamma^d per element.
-void launch_kelly(const AdaptDev& a, const SysDesc* sys, int n_sys, int nel_max, const double* x, double* gamma,
-                  hipStream_t st);
+int kelly_patches(int nelx, int nely);  // blocks of launch_kelly per system
+void launch_kelly(const AdaptDev& a, const SysDesc* sys, int n_sys, int n_patch, int p_max, const double* x,
+                  double* gamma, hipStream_t st);
 void launch_density_indicator(const AdaptDev& a, const double* rho, const DensityBounds& b, double* gamma,
                               int64_t n_el, hipStream_t st);
 void launch_gather_free(const PcgDev& s, const int32_t* free_to_full, const double* ufull, double* xfree,

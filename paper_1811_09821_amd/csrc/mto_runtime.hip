@@ -1821,9 +1821,10 @@ int mto_kelly_indicator(mto_plan* P, const double* u, double* gamma, void* strea
   if ((rc = qr_setup(P)) || (rc = adapt_setup(P))) return rc;
   hipStream_t st = (hipStream_t)stream;
   launch_gather_free(P->pcg(), P->f2f, u, P->q, st);
-  int nel_max = 0;
-  for (int i = 0; i < P->n_inst; ++i) nel_max = std::max(nel_max, P->inst_nelx[i] * P->inst_nely[i]);
-  launch_kelly(adapt_dev(P), P->d_sys, P->n_sys, nel_max, P->q, gamma, st);
+  int n_patch = 0, p_max = 1;
+  for (int i = 0; i < P->n_inst; ++i) n_patch = std::max(n_patch, kelly_patches(P->inst_nelx[i], P->inst_nely[i]));
+  for (const GroupHost& g : P->groups) p_max = std::max(p_max, g.p);
+  launch_kelly(adapt_dev(P), P->d_sys, P->n_sys, n_patch, p_max, P->q, gamma, st);
   return check_launch("kelly_indicator");
 }
 
