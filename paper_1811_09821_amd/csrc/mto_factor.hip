@@ -33,6 +33,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mto_device.hpp"
 #include "mto_kernels.hpp"
@@ -367,6 +368,150 @@ __global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_factored(const FacTi
   factored_tile<1, true, VERT>(t, E, xin, s, mode, it_k, lds);
 }
 
+// Sensitivity: w_s = lam_e^T K_s u_e for every cell s of every column, g =
+// -E'(rho) w.  With K_s as above, a row sy of cells needs for the x factors
+// a, b, c the n x n matrices Z_t(i, k) = sum over j, l, components of lam_ij
+// y_t(j, l) u_kl; then w = sum_t t_x^(sx) : Z_t, d of them from one Z: d (16 n^3
+// + (2 n^2 + n) d) multiply-adds per column (11.4 k at p = 4, d = 5; 62.5 k for
+// the cells' dense matrices).  One lane takes a column, the waves of a block
+// take the rows of cells of its 64 columns in turn; a component of u and Z are
+// in registers, u and lam in LDS (once where they are the same vector, SAME: the
+// arithmetic does not differ).  Both have their rigid motions removed first, as in
+// k_elem_dd: K_s annihilates them exactly, its FP64 rounding does not.
+template <int P, bool SAME>
+__device__ __forceinline__ void sens_tile(const FacTile& t, const double* __restrict__ dE,
+                                          const double* __restrict__ x, const double* __restrict__ y,
+                                          double* __restrict__ gout, const SysDesc* __restrict__ sys, double* ush) {
+  constexpr int n = P + 1, NE = ne_of(P), NS = n * (n + 1) / 2, XT = fac_x_of(P), YT = fac_y_of(P);
+  constexpr int NV = SAME ? 1 : 2, GB = (NE + 3) / 4;
+  const int W = blockDim.x >> 6, lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const bool valid = lane < t.count;
+  const int el = valid ? lane : t.count - 1;  // idle lanes repeat the last column, unstored
+  const double* __restrict__ xs = x + t.dof_off;
+  const double* __restrict__ ys_ = y + t.dof_off;
+  const int32_t* __restrict__ gi_ = t.gidx + el;
+  const int64_t cell = t.cell[el];
+  const int64_t g_off = sys[t.sys].g_off;
+  for (int r0 = wave; r0 < NE; r0 += W * GB) {
+    int gi[GB];
+    double v[NV][GB];
+#pragma unroll
+    for (int q = 0; q < GB; ++q) gi[q] = gi_[(int64_t)min(r0 + W * q, NE - 1) * t.npad];
+#pragma unroll
+    for (int q = 0; q < GB; ++q) {
+      v[0][q] = xs[max(gi[q], 0)];
+      if (!SAME) v[NV - 1][q] = ys_[max(gi[q], 0)];
+    }
+#pragma unroll
+    for (int q = 0; q < GB; ++q)
+      if (r0 + W * q < NE)
+#pragma unroll
+        for (int h = 0; h < NV; ++h) ush[(h * NE + r0 + W * q) * 64 + lane] = gi[q] >= 0 ? v[h][q] : 0.0;
+  }
+  __syncthreads();
+  {  // rigid motion removed from the vertex rows
+    double x0[NV], x1[NV], th[NV];
+#pragma unroll
+    for (int h = 0; h < NV; ++h) {
+      const double* b = ush + h * NE * 64 + lane;
+      x0[h] = b[0];
+      x1[h] = b[64];
+      th[h] = b[3 * 64] - x1[h];
+    }
+    __syncthreads();
+    for (int v = wave; v < 8; v += W) {
+      const int row = vertex_dof<P>(v);
+#pragma unroll
+      for (int h = 0; h < NV; ++h) {
+        double* b = ush + (h * NE + row) * 64 + lane;
+        *b = rigid_free<P>(*b, row, x0[h], x1[h], th[h]);
+      }
+    }
+    __syncthreads();
+  }
+  const cptr tab = scalar_table(t.kfac);
+  const int d = t.d;
+#pragma unroll 1
+  for (int sy = wave; sy < d; sy += W) {
+    double Z[2 * NS + n * n];
+#pragma unroll
+    for (int q = 0; q < 2 * NS + n * n; ++q) Z[q] = 0.0;
+    cptr ys = tab + d * XT + sy * n * YT;
+    auto half = [&](auto comp) {  // the part of u's component C
+      constexpr int C = decltype(comp)::value;
+      lds_vec up = (lds_vec)(ush + lane), lp = (lds_vec)(ush + (NV - 1) * NE * 64 + lane);
+      asm volatile("" : "+v"(up));
+      double u[n][n];
+#pragma unroll
+      for (int l = 0; l < n; ++l)
+#pragma unroll
+        for (int k = 0; k < n; ++k) u[l][k] = up[(2 * (l * n + k) + C) * 64];
+#pragma unroll 1
+      for (int j = 0; j < n; ++j) {
+        double lm[2][n];  // lam's components C, 1 - C of function row j
+#pragma unroll
+        for (int i = 0; i < n; ++i) {
+          lm[0][i] = lp[(2 * (j * n + i) + C) * 64];
+          lm[1][i] = lp[(2 * (j * n + i) + 1 - C) * 64];
+        }
+        double T[4][n];
+#pragma unroll
+        for (int l = 0; l < n; ++l)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            // x: D11 b, D33 a, D12 c, D33 c^T; y: D33 b, D11 a, D33 c, D12 c^T (rows j, columns l)
+            const double m = ys[j * YT + (2 * q + C) * n + l];
+#pragma unroll
+            for (int k = 0; k < n; ++k) T[q][k] = l == 0 ? m * u[0][k] : fma(m, u[l][k], T[q][k]);
+          }
+#pragma unroll
+        for (int i = 0; i < n; ++i)
+#pragma unroll
+          for (int k = 0; k < n; ++k) {
+            const int sym = sym_index(n, i, k);
+            Z[sym] = fma(lm[0][i], T[0][k], Z[sym]);
+            Z[NS + sym] = fma(lm[0][i], T[1][k], Z[NS + sym]);
+            double &z1 = Z[2 * NS + k * n + i], &z2 = Z[2 * NS + i * n + k];
+            z1 = fma(lm[1][i], T[2][k], z1);
+            z2 = fma(lm[1][i], T[3][k], z2);
+          }
+      }
+#pragma unroll
+      for (int q = 0; q < 2 * NS + n * n; ++q) asm volatile("" : "+v"(Z[q]));
+    };
+    half(std::integral_constant<int, 0>{});
+    half(std::integral_constant<int, 1>{});
+    const int64_t c0 = cell + sy * d;
+#pragma unroll 1
+    for (int sx = 0; sx < d; ++sx) {
+      const double de = dE[c0 + sx];
+      cptr xt = tab + sx * XT;
+      double w = 0.0;
+#pragma unroll
+      for (int q = 0; q < 2 * NS + n * n; ++q) w = fma(xt[q], Z[q], w);
+      if (valid) gout[g_off + c0 + sx] = -de * w;
+    }
+  }
+}
+
+template <int PM, bool SAME>
+__global__ __launch_bounds__(64 * SENS_MAX_W, 2) void k_sens(const FacTile* __restrict__ tiles, int n_tiles, int xcd_run,
+                                                            const double* __restrict__ dE,
+                                                            const double* __restrict__ x, const double* __restrict__ y,
+                                                            double* __restrict__ gout,
+                                                            const SysDesc* __restrict__ sys) {
+  extern __shared__ double lds[];
+  const FacTile t = tiles[xcd_tile(blockIdx.x, n_tiles, xcd_run)];
+  if constexpr (PM >= 4)
+    if (t.p == 4) return sens_tile<4, SAME>(t, dE, x, y, gout, sys, lds);
+  if constexpr (PM >= 3)
+    if (t.p == 3) return sens_tile<3, SAME>(t, dE, x, y, gout, sys, lds);
+  if constexpr (PM >= 2)
+    if (t.p == 2) return sens_tile<2, SAME>(t, dE, x, y, gout, sys, lds);
+  sens_tile<1, SAME>(t, dE, x, y, gout, sys, lds);
+}
+
 }  // namespace
 
 namespace {
@@ -399,6 +544,31 @@ void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd
 void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E,
                             const double* dz, const PcgDev& s, hipStream_t st) {
   launch_factored<true>(tiles, f, xcd_run, E, dz, s, ELEM_APPLY_RUNNING, 0, st, nullptr, nullptr);
+}
+
+// Up to 256 tiles (one per CU) each row of cells has its own wave; beyond, a
+// wave takes two, which keeps more columns' gathers in flight.  Measured (us),
+// a dense K_s contraction per cell and a launch per group -> this:
+//   160 x 80 mesh, p = 3, d = 4: 21.9 -> 9.4 (half of it the gather)
+//   400 x 200 mesh, p = 1..4, three systems: 250 -> 60
+//   16 designs, p = 4 in the main, two systems: 560 -> 158
+void launch_sens(const FacTile* tiles, const FactoredLaunch& f, int d_max, int xcd_run, const double* dE,
+                 const double* x, const double* y, double* gout, const SysDesc* sys, hipStream_t st) {
+  const int n = f.n_split + f.n_whole;
+  if (n == 0) return;
+  const int waves = std::min(n <= 256 ? d_max : (d_max + 1) / 2, SENS_MAX_W);
+  const bool same = x == y;
+  const dim3 grid(n), block(64 * waves);
+  const uint32_t lds = (uint32_t)(8 * 64 * ne_of(f.p_max) * (same ? 1 : 2));
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, grid, block, lds, st, tiles + f.tile_begin, n, xcd_run, dE, x, y, gout, sys);
+  };
+  switch (f.p_max) {
+    case 1: same ? go(k_sens<1, true>) : go(k_sens<1, false>); break;
+    case 2: same ? go(k_sens<2, true>) : go(k_sens<2, false>); break;
+    case 3: same ? go(k_sens<3, true>) : go(k_sens<3, false>); break;
+    default: same ? go(k_sens<4, true>) : go(k_sens<4, false>); break;
+  }
 }
 
 }  // namespace mto

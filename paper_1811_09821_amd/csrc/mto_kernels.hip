@@ -803,89 +803,6 @@ __global__ __launch_bounds__(64) void k_elem_plain(GroupDev g, const Tile* __res
   }
 }
 
-// ---------------------------------------------------------------------------
-// Sensitivity: w_{e,s} = lam_e^T K_s u_e (lam = u for compliance) with K_s u_e on MFMA (same A fragments
-// as the matvec), then a segmented dot over the rows each lane holds and a
-// 4-lane butterfly; g = -E'(rho) w.  Both element vectors have their rigid
-// motions (through DOFs 0, 1 and 3) removed first, as in k_elem_dd: K_s
-// annihilates them exactly, its FP64 rounding does not.
-template <int P, int NC>
-__global__ __launch_bounds__(BLOCK) void k_sens_mfma(GroupDev g, const Tile* __restrict__ tiles,
-                                                    const double* __restrict__ dE, const double* __restrict__ x,
-                                                    const double* __restrict__ y, double* __restrict__ gout,
-                                                    const SysDesc* __restrict__ sys) {
-  constexpr int NEP = nep_of(P), MB = mb_of(P), NJ = NEP / 4;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int tix = blockIdx.x * WAVES + wave;
-  if (tix >= g.n_tiles) return;
-  const Tile t = tiles[g.tile_begin + tix];
-  const SysDesc& sd = sys[t.sys];
-  const int n = lane & 15, kq = lane >> 4;
-  const double* __restrict__ xs = x + t.dof_off;
-  const double* __restrict__ ys = y + t.dof_off;
-  double u[NC][NJ], lm[NC][NJ];
-  int cellb[NC];
-  bool valid[NC];
-#pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int col = c * 16 + n;
-    valid[c] = col < t.count;
-    const int el = t.elem_begin + col;
-    cellb[c] = valid[c] ? g.cell[el] : 0;
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-      const int gi = valid[c] ? g.gidx[(4 * jj + kq) * g.npad + el] : -1;
-      u[c][jj] = gi >= 0 ? xs[gi] : 0.0;
-      lm[c][jj] = gi >= 0 ? ys[gi] : 0.0;
-    }
-    // rows 0, 1, 3 of column n sit in lanes n, 16 + n, 48 + n (k-step 0)
-    const double ua = __shfl(u[c][0], n), ub = __shfl(u[c][0], 16 + n), uth = __shfl(u[c][0], 48 + n) - ub;
-    const double la = __shfl(lm[c][0], n), lb = __shfl(lm[c][0], 16 + n), lth = __shfl(lm[c][0], 48 + n) - lb;
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-      u[c][jj] = rigid_free<P>(u[c][jj], 4 * jj + kq, ua, ub, uth);
-      lm[c][jj] = rigid_free<P>(lm[c][jj], 4 * jj + kq, la, lb, lth);
-    }
-  }
-  const double* __restrict__ kf = g.kfrag + lane;
-  for (int sc = 0; sc < g.S; ++sc) {
-    d4 acc[MB][NC];
-#pragma unroll
-    for (int b = 0; b < MB; ++b)
-#pragma unroll
-      for (int c = 0; c < NC; ++c) acc[b][c] = d4{0.0, 0.0, 0.0, 0.0};
-    const double* __restrict__ kfs = kf + (size_t)sc * NJ * MB * 64;
-#pragma unroll
-    for (int jj = 0; jj < NJ; ++jj) {
-      double a[MB];
-#pragma unroll
-      for (int b = 0; b < MB; ++b) a[b] = kfs[(jj * MB + b) * 64];
-#pragma unroll
-      for (int c = 0; c < NC; ++c)
-#pragma unroll
-        for (int b = 0; b < MB; ++b)
-          acc[b][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[b], u[c][jj], acc[b][c], 0, 0, 0);
-    }
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      double w = 0.0;
-#pragma unroll
-      for (int b = 0; b < MB; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int jr = 4 * b + r;  // row 16b + kq + 4r = 4 jr + kq, held in u[c][jr]
-          if (jr < NJ) w = fma(lm[c][jr < NJ ? jr : 0], acc[b][c][r], w);
-        }
-      w += __shfl_xor(w, 16);
-      w += __shfl_xor(w, 32);
-      if (kq == 0 && valid[c]) {
-        const int64_t cell = (int64_t)cellb[c] + sc;
-        gout[sd.g_off + cell] = -dE[cell] * w;
-      }
-    }
-  }
-}
-
 // Jacobi diagonal contributions: thread per element column of a load-0 system.
 template <int P>
 __global__ __launch_bounds__(64) void k_diag_elem(GroupDev g, const Tile* __restrict__ tiles,
@@ -1414,16 +1331,6 @@ void launch_elem_p(const GroupDev& g, int path, int ncol, const Tile* tiles, con
   }
 }
 
-template <int P>
-void launch_sens_p(const GroupDev& g, int ncol, const Tile* tiles, const double* dE, const double* x,
-                   const double* y, double* gout, const SysDesc* sys, hipStream_t st) {
-  const dim3 grid(nblocks(g.n_tiles, WAVES)), block(BLOCK);
-  switch (ncol) {
-    case 1: hipLaunchKernelGGL((k_sens_mfma<P, 1>), grid, block, 0, st, g, tiles, dE, x, y, gout, sys); break;
-    case 2: hipLaunchKernelGGL((k_sens_mfma<P, 2>), grid, block, 0, st, g, tiles, dE, x, y, gout, sys); break;
-    default: hipLaunchKernelGGL((k_sens_mfma<P, 4>), grid, block, 0, st, g, tiles, dE, x, y, gout, sys); break;
-  }
-}
 
 }  // namespace
 
@@ -1466,17 +1373,6 @@ void launch_elem_assemble(const GroupDev& g, const double* E, double* kst, hipSt
     case 2: hipLaunchKernelGGL(k_elem_assemble<2>, grid, block, 0, st, g, E, kst); break;
     case 3: hipLaunchKernelGGL(k_elem_assemble<3>, grid, block, 0, st, g, E, kst); break;
     default: hipLaunchKernelGGL(k_elem_assemble<4>, grid, block, 0, st, g, E, kst); break;
-  }
-}
-
-void launch_sens(const GroupDev& g, const Tile* tiles, const double* dE, const double* x, const double* y,
-                 double* gout, const SysDesc* sys, hipStream_t st) {
-  if (g.n_tiles == 0) return;
-  switch (g.p) {
-    case 1: launch_sens_p<1>(g, g.ncol, tiles, dE, x, y, gout, sys, st); break;
-    case 2: launch_sens_p<2>(g, g.ncol, tiles, dE, x, y, gout, sys, st); break;
-    case 3: launch_sens_p<3>(g, g.ncol, tiles, dE, x, y, gout, sys, st); break;
-    default: launch_sens_p<4>(g, g.ncol, tiles, dE, x, y, gout, sys, st); break;
   }
 }
 

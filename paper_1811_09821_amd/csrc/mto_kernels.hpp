@@ -242,9 +242,11 @@ void launch_elem_stored(const GroupDev& g, const Tile* tiles, const double* xin,
 void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run, const double* E,
                             const double* dz, const PcgDev& s, hipStream_t st);
 // g = -E' lam_e^T K_s u_e per system, u from x and lam from y (free-DOF
-// layout of the systems; y = x gives the compliance sensitivity)
-void launch_sens(const GroupDev& g, const Tile* tiles, const double* dE, const double* x, const double* y,
-                 double* gout, const SysDesc* sys, hipStream_t st);
+// layout of the systems; y = x gives the compliance sensitivity), over the
+// tiles of every group; d_max the largest d
+constexpr int SENS_MAX_W = 8;  // waves per tile
+void launch_sens(const FacTile* tiles, const FactoredLaunch& f, int d_max, int xcd_run, const double* dE,
+                 const double* x, const double* y, double* gout, const SysDesc* sys, hipStream_t st);
 // per element, sum_s E_s table[s][row] into the slots of load-0 systems
 // (table = diag(K_s) for Jacobi, row sums of |K_s| for the l1 smoother)
 void launch_diag_elem(const GroupDev& g, const Tile* tiles, const double* E, double* slots, const SysDesc* sys,

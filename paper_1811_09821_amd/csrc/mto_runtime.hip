@@ -426,9 +426,9 @@ int rebuild_tiles(mto_plan* P) {
     }
     P->fused_n_tiles = (int)P->tiles.size() - P->fused_tile_begin;
   }
-  if (P->prm.kernel_path == MTO_PATH_MFMA) {
-    // the same 64-column tiles for the sum-factorised product and vertex update (its descriptors carry
-    // the group's arrays): the tiles that may go one to a wave last, the rest by decreasing work
+  {
+    // the same 64-column tiles for the sum-factorised kernels (their descriptors carry the group's
+    // arrays): the tiles that may go one to a wave last, the rest by decreasing work
     std::vector<int> order(P->groups.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
@@ -1326,13 +1326,18 @@ void enq_restart(mto_plan* P, hipStream_t st) {
   if (P->prm.precond != MTO_PRECOND_JACOBI) enq_vcycle(P, 0, 1, st);
 }
 
+void enq_sens(mto_plan* P, const double* u, const double* lam, double* g, hipStream_t st) {
+  int d_max = 1;
+  for (const GroupHost& gr : P->groups) d_max = std::max(d_max, gr.d);
+  launch_sens(P->d_fac_tiles, P->fac_all, d_max, P->n_sys > 1 ? 8 : 0, P->dE, u, lam, g, P->d_sys, st);
+}
+
 void enq_outputs(mto_plan* P, double* u, double* c, double* g, hipStream_t st) {
   const PcgDev s = P->pcg();
   launch_compliance(s, c, st);
   launch_fill(u, 0.0, P->n_u, st);
   launch_scatter_full(s, P->f2f, P->xs_hi, u, st);
-  if (g)
-    for (auto& gr : P->groups) launch_sens(P->gdev(gr), P->d_tiles, P->dE, P->xs_hi, P->xs_hi, g, P->d_sys, st);
+  if (g) enq_sens(P, P->xs_hi, P->xs_hi, g, st);
 }
 
 int capture(mto_plan* P, hipGraphExec_t* exec, const std::function<void(hipStream_t)>& body) {
@@ -1737,7 +1742,7 @@ int mto_sensitivity(mto_plan* P, const double* rho, const double* u, double* g, 
   const PcgDev s = P->pcg();
   launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
   launch_gather_free(s, P->f2f, u, P->q, st);
-  for (auto& gr : P->groups) launch_sens(P->gdev(gr), P->d_tiles, P->dE, P->q, P->q, g, P->d_sys, st);
+  enq_sens(P, P->q, P->q, g, st);
   return check_launch("sensitivity");
 }
 
@@ -1898,7 +1903,7 @@ int mto_adjoint_sensitivity(mto_plan* P, const double* rho, const double* u, con
   launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
   launch_gather_free(s, P->f2f, u, P->q, st);
   launch_gather_free(s, P->f2f, lam, P->z, st);
-  for (auto& gr : P->groups) launch_sens(P->gdev(gr), P->d_tiles, P->dE, P->q, P->z, g, P->d_sys, st);
+  enq_sens(P, P->q, P->z, g, st);
   return check_launch("adjoint_sensitivity");
 }
 
