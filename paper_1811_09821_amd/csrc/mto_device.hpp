@@ -9,6 +9,9 @@
 
 namespace mto {
 
+typedef const __attribute__((address_space(4))) double* cptr;  // read-only tables, through the scalar cache
+__device__ __forceinline__ cptr scalar_table(const double* p) { return (cptr)(uintptr_t)p; }
+
 // Sum of arr[a..b) by one wave: strided sequential sums per lane, then a xor
 // butterfly.  Every lane ends with the same bits, and so does every wave that
 // calls it on the same range.

@@ -41,9 +41,6 @@
 namespace mto {
 namespace {
 
-typedef const __attribute__((address_space(4))) double* cptr;  // read-only tables, through the scalar cache
-__device__ __forceinline__ cptr scalar_table(const double* p) { return (cptr)(uintptr_t)p; }
-
 typedef const __attribute__((address_space(3))) double* lds_vec;
 
 __host__ __device__ constexpr int sym_index(int n, int i, int k) {  // packed upper triangle by rows

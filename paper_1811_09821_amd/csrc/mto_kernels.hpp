@@ -215,7 +215,7 @@ struct FacTile {
   const int32_t* cell;
   const double* kfac;
   int64_t dof_off, slot_off;
-  int32_t npad, count, sys, pc_begin, pc_end, p, d, pad;
+  int32_t npad, count, sys, pc_begin, pc_end, p, d, group;
 };
 struct FactoredLaunch {
   int32_t tile_begin, n_split, n_whole, p_max, waves;
@@ -247,10 +247,11 @@ void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int x
 constexpr int SENS_MAX_W = 8;  // waves per tile
 void launch_sens(const FacTile* tiles, const FactoredLaunch& f, int d_max, int xcd_run, const double* dE,
                  const double* x, const double* y, double* gout, const SysDesc* sys, hipStream_t st);
-// per element, sum_s E_s table[s][row] into the slots of load-0 systems
-// (table = diag(K_s) for Jacobi, row sums of |K_s| for the l1 smoother)
-void launch_diag_elem(const GroupDev& g, const Tile* tiles, const double* E, double* slots, const SysDesc* sys,
-                      const double* table, hipStream_t st);
+// per element, sum_s E_s table[s][row] into the slots of load-0 systems, table =
+// diag(K_s) (Jacobi) or, abs_rows, the row sums of |K_s| (l1 smoother), over
+// the tiles of every group
+void launch_diag_elem(const FacTile* tiles, const FactoredLaunch& f, const GroupDev* groups, const double* E,
+                      double* slots, const SysDesc* sys, int abs_rows, hipStream_t st);
 
 // E, E' of every cell (Sec. 2.2); bad (device int, may be NULL) is set to 1 if a
 // density is not finite or outside [0, 1] (it is never cleared here)

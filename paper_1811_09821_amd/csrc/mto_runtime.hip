@@ -448,7 +448,7 @@ int rebuild_tiles(mto_plan* P) {
             const SysDesc& sd = P->sys[sysi];
             for (int e = g.inst_begin[i]; e < g.inst_begin[i + 1]; e += 64)
               ft.push_back(FacTile{g.gidx + e, g.sidx + e, g.cell + e, g.kfac, sd.dof_off, sd.slot_off, g.npad,
-                                   std::min(64, g.inst_begin[i + 1] - e), sysi, sd.chunk_begin, sd.chunk_end, g.p, g.d, 0});
+                                   std::min(64, g.inst_begin[i + 1] - e), sysi, sd.chunk_begin, sd.chunk_end, g.p, g.d, gi});
           }
         g.fac_n_tiles = (int)ft.size() - g.fac_tile_begin;
         gs.push_back(&g);
@@ -1244,8 +1244,7 @@ void enq_setup(mto_plan* P, const double* rho, const double* u0, hipStream_t st)
   // l1-Jacobi level-0 smoother of MTO_PRECOND_MG unless a damping factor is set
   const bool l1 = P->prm.precond == MTO_PRECOND_MG && !(P->prm.mg_omega > 0.0);
   const bool damped = P->prm.precond == MTO_PRECOND_MG && !l1;
-  for (auto& g : P->groups)
-    launch_diag_elem(P->gdev(g), P->d_tiles, P->E, P->slots, P->d_sys, l1 ? g.kabs : g.kdiag, st);
+  launch_diag_elem(P->d_fac_tiles, P->fac_all, P->d_groups_cur, P->E, P->slots, P->d_sys, l1, st);
   launch_dinv(s, P->dinv, damped ? P->prm.mg_omega : 1.0, st);
   // The multigrid set-up depends only on the moduli, as do the Schwarz block
   // inverses.  The coarsest factor is one workgroup on a serial chain that
@@ -1886,7 +1885,7 @@ int mto_jacobi_diagonal(mto_plan* P, const double* rho, double* diag, void* stre
   hipStream_t st = (hipStream_t)stream;
   const PcgDev s = P->pcg();
   launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
-  for (auto& g : P->groups) launch_diag_elem(P->gdev(g), P->d_tiles, P->E, P->slots, P->d_sys, g.kdiag, st);
+  launch_diag_elem(P->d_fac_tiles, P->fac_all, P->d_groups_cur, P->E, P->slots, P->d_sys, 0, st);
   int64_t acc = 0;
   for (int i = 0; i < P->n_inst; ++i) acc += P->n_dof[i];
   launch_fill(diag, 0.0, acc, st);
