@@ -55,6 +55,13 @@ constexpr int fac_table_of(int p, int d) { return (d * (fac_x_of(p) + (p + 1) * 
 // ks[s*ne*ne + i*ne + j] for density cell s of a d x d grid.
 std::vector<double> subcell_tables(int p, int d, double nu);
 
+// The 1D integrals of order q in MFMA fragment order for the QR-error
+// indicator's K' (k_qr): for t = a, b, c, c^T, tiles of 16 (i, k) and halves h
+// of the cells, B fragments t(i, k) of cell sx = 4 h + l / 16; then, for the
+// component pairs xx, xy, yx, yy, tiles of 16 pairs j >= l, the two terms and h,
+// A fragments of the y factors of cell sy = 4 h + l / 16.
+std::vector<double> qr_fragments(int q, int d, double nu);
+
 // Load transfer of the QR-error indicator (Sec. 3.2.3): the order-(p+1)
 // element load integrates the order-p load field against the refined
 // functions.  In 1D, with the hierarchic functions phi_0..phi_p of order p

@@ -51,12 +51,12 @@ struct GroupDev {
   const int32_t* cell;     // [npad] first density cell (global)
 };
 
-// One (p, d) group for the QR-error indicator: order-(p+1) cell tables and
-// the instance and element of every group column.
+// One (p, d) group for the QR-error indicator: order-(p+1) tables and the
+// instance and element of every group column.
 struct QrGroupDev {
   int32_t p, d, S, npad;
   int32_t n_elems;
-  const double* tab;      // [S][NT] packed lower triangle of K_s^(p+1), (i, j <= i) at i (i+1)/2 + j
+  const double* tab;      // 1D integrals of order p + 1 (qr_fragments)
   const int32_t* gidx;    // as GroupDev::gidx
   const int32_t* cell;    // as GroupDev::cell
   const int32_t* eid;     // [n_elems] element index within its instance

@@ -1762,13 +1762,7 @@ static int qr_setup(mto_plan* P) {
   if (P->qr_ready) return MTO_OK;
   int rc;
   for (auto& g : P->groups) {
-    const int q = g.p + 1, nq = ne_of(q), nt = nq * (nq + 1) / 2;
-    const std::vector<double> ks = subcell_tables(q, g.d, P->prm.nu);
-    std::vector<double> packed((size_t)g.S * nt);
-    for (int s = 0; s < g.S; ++s)
-      for (int i = 0; i < nq; ++i)
-        for (int j = 0; j <= i; ++j) packed[(size_t)s * nt + i * (i + 1) / 2 + j] = ks[((size_t)s * nq + i) * nq + j];
-    if ((rc = dev_upload(P, &g.qtab, packed)) || (rc = dev_upload(P, &g.d_eid, g.eid_h)) ||
+    if ((rc = dev_upload(P, &g.qtab, qr_fragments(g.p + 1, g.d, P->prm.nu))) || (rc = dev_upload(P, &g.d_eid, g.eid_h)) ||
         (rc = dev_upload(P, &g.d_einst, g.einst_h)))
       return rc;
   }

@@ -157,6 +157,40 @@ std::vector<double> factor_tables(int p, int d, double nu) {
   return out;
 }
 
+std::vector<double> qr_fragments(int q, int d, double nu) {
+  const int n = q + 1, X = fac_x_of(q), Y = fac_y_of(q), NS = n * (n + 1) / 2;
+  const int CT = (n * n + 15) / 16, RT = (NS + 15) / 16;
+  const std::vector<double> f = factor_tables(q, d, nu);
+  std::vector<double> out((size_t)(4 * CT * 2 + 16 * RT) * 64, 0.0);
+  for (int t = 0; t < 4; ++t)
+    for (int ct = 0; ct < CT; ++ct)
+      for (int h = 0; h < 2; ++h)
+        for (int l = 0; l < 64; ++l) {
+          const int sx = 4 * h + l / 16, ik = 16 * ct + l % 16, i = ik / n, k = ik % n;
+          if (sx >= d || ik >= n * n) continue;
+          const int lo = std::min(i, k), hi = std::max(i, k), sym = lo * n - lo * (lo - 1) / 2 + hi - lo;
+          const int at = t < 2 ? t * NS + sym : 2 * NS + (t == 2 ? i * n + k : k * n + i);
+          out[(size_t)((t * CT + ct) * 2 + h) * 64 + l] = f[(size_t)sx * X + at];
+        }
+  // columns of the y factors: (a_x, b_x), (c, c^T), (c^T, c), (a_x, b_x) for xx, xy, yx, yy
+  const int term[4][2] = {{0, 2}, {7, 5}, {4, 6}, {1, 3}};
+  double* y = &out[(size_t)4 * CT * 2 * 64];
+  for (int cc = 0; cc < 4; ++cc)
+    for (int rt = 0; rt < RT; ++rt)
+      for (int t = 0; t < 2; ++t)
+        for (int h = 0; h < 2; ++h)
+          for (int l = 0; l < 64; ++l) {
+            const int sy = 4 * h + l / 16, pr = 16 * rt + l % 16;
+            if (sy >= d || pr >= NS) continue;
+            int j = 0;
+            while ((j + 1) * (j + 2) / 2 <= pr) ++j;
+            const int m = pr - j * (j + 1) / 2;  // pair (j, m), m <= j: table row j, column m
+            y[(size_t)((cc * RT + rt) * 4 + 2 * t + h) * 64 + l] =
+                f[(size_t)d * X + (size_t)sy * n * Y + (size_t)j * Y + term[cc][t] * n + m];
+          }
+  return out;
+}
+
 std::vector<double> qr_load_transfer(int p) {
   // 1D mass matrix of the order-(p+1) functions on the unit interval
   // (dx = dxi / 2), exact with p + 2 Gauss points (degree 2p + 2)
