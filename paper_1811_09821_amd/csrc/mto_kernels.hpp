@@ -257,6 +257,21 @@ void launch_diag_elem(const FacTile* tiles, const FactoredLaunch& f, const Group
 // density is not finite or outside [0, 1] (it is never cleared here)
 void launch_simp(const double* rho, double* E, double* dE, int64_t n, double E0, double Emin, double q,
                  hipStream_t st, int32_t* bad = nullptr);
+// Inputs of a single product or sensitivity (launch_inputs): E and E' of every
+// cell (as launch_simp), the free DOFs of up to two full vectors (absent ones
+// NULL), and up to two arrays set to zero (absent ones of length 0).
+struct InputsDev {
+  const double* rho;
+  double *E, *dE;
+  int64_t n_cells;
+  double E0, Emin, q;
+  const double* full[2];
+  double* free[2];
+  double* zero[2];
+  int64_t n_zero[2];
+  int64_t simp_blocks;  // set by launch_inputs
+};
+void launch_inputs(const PcgDev& s, const int32_t* free_to_full, InputsDev in, hipStream_t st);
 void launch_fill(double* a, double v, int64_t n, hipStream_t st);
 void launch_fill_i32(int32_t* a, int32_t v, int64_t n, hipStream_t st);
 // dinv = scale / (sum of slots) on the first system of each instance

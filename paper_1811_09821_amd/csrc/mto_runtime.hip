@@ -1136,6 +1136,33 @@ int ensure_stored(mto_plan* P, GroupHost& g) {
   return MTO_OK;
 }
 
+// The densities and one full vector of a single call.
+InputsDev inputs(const mto_plan* P, const double* rho, double* E, double* dE, const double* full, double* free) {
+  InputsDev in{};
+  in.rho = rho;
+  in.E = E;
+  in.dE = dE;
+  in.n_cells = P->n_cells_tot;
+  in.E0 = P->prm.E0;
+  in.Emin = P->prm.Emin;
+  in.q = P->prm.q;
+  in.full[0] = full;
+  in.free[0] = free;
+  return in;
+}
+
+// An output that a product fills at the free DOFs only: cleared with the
+// inputs, or, where it overlaps one of them (y = x), once they are read.
+bool clear_with_inputs(const mto_plan* P, const double* rho, const double* x, double* y, InputsDev& in) {
+  auto apart = [&](const double* a, int64_t n) {
+    return (uintptr_t)(a + n) <= (uintptr_t)y || (uintptr_t)(y + P->n_u) <= (uintptr_t)a;
+  };
+  if (!apart(rho, P->n_cells_tot) || !apart(x, P->n_u)) return false;
+  in.zero[0] = y;
+  in.n_zero[0] = P->n_u;
+  return true;
+}
+
 void enq_assemble_stored(mto_plan* P, hipStream_t st) {
   if (P->prm.kernel_path != MTO_PATH_MFMA) return;
   for (auto& g : P->groups)
@@ -1669,11 +1696,12 @@ int mto_apply_stiffness(mto_plan* P, const double* rho, const double* x, double*
   if (!P || !rho || !x || !y) return fail(MTO_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   const PcgDev s = P->pcg();
-  launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
+  InputsDev in = inputs(P, rho, P->E, P->dE, x, P->q);
+  const bool cleared = clear_with_inputs(P, rho, x, y, in);
+  launch_inputs(s, P->f2f, in, st);
   enq_assemble_stored(P, st);
-  launch_gather_free(s, P->f2f, x, P->q, st);
   enq_elem_all(P, P->q, ELEM_APPLY, 0, st);
-  launch_fill(y, 0.0, P->n_u, st);
+  if (!cleared) launch_fill(y, 0.0, P->n_u, st);
   launch_assemble_to_full(s, P->f2f, y, 0, st);
   return check_launch("apply_stiffness");
 }
@@ -1733,15 +1761,17 @@ int mto_apply_stiffness_noalloc(mto_plan* P, const double* rho, const double* x,
   PcgDev s = P->pcg();
   s.q = q;
   s.slots = slots;
-  launch_simp(rho, E, dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
-  launch_gather_free(s, P->f2f, x, q, st);
+  InputsDev in = inputs(P, rho, E, dE, x, q);
+  const bool cleared = clear_with_inputs(P, rho, x, y, in);
   // slots that no element writes (missing neighbours) must read as zero; the
   // array keeps the previous call's contents
-  launch_fill(slots, 0.0, P->n_slots_tot, st);
+  in.zero[1] = slots;
+  in.n_zero[1] = P->n_slots_tot;
+  launch_inputs(s, P->f2f, in, st);
   launch_elem_factored(P->d_fac_tiles, P->fac, P->n_sys > 1 ? 8 : 0, E, q, s, ELEM_APPLY, 0, st);
   for (auto& g : P->groups)
     if (!g.factored) launch_elem(P->gdev(g), P->prm.kernel_path, P->d_tiles, E, q, s, ELEM_APPLY, 0, st);
-  launch_fill(y, 0.0, P->n_u, st);
+  if (!cleared) launch_fill(y, 0.0, P->n_u, st);
   launch_assemble_to_full(s, P->f2f, y, 0, st);
   return check_launch("apply_stiffness_noalloc");
 }
@@ -1751,8 +1781,7 @@ int mto_sensitivity(mto_plan* P, const double* rho, const double* u, double* g, 
   if (!P || !rho || !u || !g) return fail(MTO_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   const PcgDev s = P->pcg();
-  launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
-  launch_gather_free(s, P->f2f, u, P->q, st);
+  launch_inputs(s, P->f2f, inputs(P, rho, P->E, P->dE, u, P->q), st);
   enq_sens(P, P->q, P->q, g, st);
   return check_launch("sensitivity");
 }
@@ -1864,8 +1893,7 @@ int mto_qr_error(mto_plan* P, const double* rho, const double* u, double* eps, v
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   const PcgDev s = P->pcg();
-  launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
-  launch_gather_free(s, P->f2f, u, P->q, st);
+  launch_inputs(s, P->f2f, inputs(P, rho, P->E, P->dE, u, P->q), st);
   for (auto& g : P->groups) {
     QrGroupDev qd{};
     qd.p = g.p;
@@ -1905,9 +1933,10 @@ int mto_adjoint_sensitivity(mto_plan* P, const double* rho, const double* u, con
   if (!P || !rho || !u || !lam || !g) return fail(MTO_EINVAL, "NULL argument");
   hipStream_t st = (hipStream_t)stream;
   const PcgDev s = P->pcg();
-  launch_simp(rho, P->E, P->dE, P->n_cells_tot, P->prm.E0, P->prm.Emin, P->prm.q, st);
-  launch_gather_free(s, P->f2f, u, P->q, st);
-  launch_gather_free(s, P->f2f, lam, P->z, st);
+  InputsDev in = inputs(P, rho, P->E, P->dE, u, P->q);
+  in.full[1] = lam;
+  in.free[1] = P->z;
+  launch_inputs(s, P->f2f, in, st);
   enq_sens(P, P->q, P->z, g, st);
   return check_launch("adjoint_sensitivity");
 }
