@@ -171,6 +171,7 @@ struct mto_plan {
   hipEvent_t ev[N_PROG] = {};
   // per-iteration decrease of log(rr / tol2) seen last (0: none yet)
   double rate_hint = 0.0;
+  bool short_first = false;  // the last solve converged within the short chunk
   hipStream_t cap_stream = nullptr;
   // the multigrid set-up runs on side_stream beside the Schwarz block inverses
   hipStream_t side_stream = nullptr;
@@ -1443,20 +1444,18 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
       // the latest report against the newest one at least G iterations older
       size_t j = hist.size() - 2;
       while (j > 0 && hist.back().first - hist[j].first < G) --j;
-      if (hist.back().first - hist[j].first >= G)
-        rate = std::log(hist[j].second / hist.back().second) / double(hist.back().first - hist[j].first);
+      rate = std::log(hist[j].second / hist.back().second) / double(hist.back().first - hist[j].first);
     }
     if (!(rate > 0.0 && std::isfinite(rate))) rate = P->rate_hint;
     if (rate > 0.0 && !hist.empty()) {
       const double need = std::ceil(std::log(hist.back().second) / rate);  // >= 1: the ratio is > 1
       if (need < double(cap)) target = std::min(target, hist.back().first + (int64_t)need);
-    } else if (known == 0) {
-      // nothing is known yet of how fast this plan converges: the short chunk
-      // alone first.  Where that is all it takes, the 14 further iterations
-      // would pass through the device unused (20 x 10 mesh, one iteration: a
-      // solve takes 0.40 ms, 0.69 with them); elsewhere the wait costs 20 us, once per plan.
-      target = Gs;
     }
+    // The plan's last solve was over within the short chunk: that one alone
+    // first.  The 14 further iterations would pass through the device unused (20 x
+    // 10 mesh, one iteration: a solve takes 0.40 ms, 0.69 with them).  Nothing
+    // else changes where chunks end, so the bits do not either.
+    if (known == 0 && P->short_first) target = Gs;
     if (queued < target && queued < cap && n_pend < N_PROG) {
       if ((rc = launch(target - queued >= G))) return rc;
       continue;
@@ -1468,12 +1467,7 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
     HIP_TRY(hipEventSynchronize(P->ev[pd.slot]));
     known = pd.end;
     const double running = P->h_prog[2 * pd.slot], far = P->h_prog[2 * pd.slot + 1];
-    if (running == 0.0) {
-      // converged before any report: at least this fast
-      if (!(rate > 0.0 && std::isfinite(rate)) && hist.size() == 1 && hist[0].first == 0)
-        rate = std::log(hist[0].second) / double(pd.end);
-      break;
-    }
+    if (running == 0.0) break;
     if (far > 1.0 && std::isfinite(far)) hist.emplace_back(pd.end, far);
   }
   if (rate > 0.0 && std::isfinite(rate)) P->rate_hint = rate;
@@ -1533,8 +1527,10 @@ int run_solve(mto_plan* P, const double* rho, double* u, double* c, double* g, c
     }
     if ((rc = fetch(P, st, R))) return rc;
     bool any_breakdown = false, any_running = false, need_restart = false, any_bad = false;
+    if (restarts == 0) P->short_first = true;
     for (int s = 0; s < P->n_sys; ++s) {
       iters_total[s] += R.iters[s];
+      if (R.status[s] != SYS_CONVERGED || R.iters[s] > P->small_G) P->short_first = false;
       if (R.status[s] == SYS_BREAKDOWN) any_breakdown = true;
       else if (R.status[s] == SYS_RUNNING) any_running = true;
       else if (R.status[s] == SYS_BADINPUT) any_bad = true;
