@@ -375,6 +375,7 @@ struct AsmTile {
 void launch_asm_apply(const AsmTile* tiles, int n_tiles, int p_max, int xcd_run, const double* v, int resid,
                       const PcgDev& s, double* slots2, double omega, hipStream_t st);
 // z = assembled slots2 (running systems)
+void launch_asm_resid(const PcgDev& s, hipStream_t st);
 void launch_asm_z(const PcgDev& s, const double* slots2, hipStream_t st);
 // z += assembled slots2, partial sums of r.z (parity slot as k_mg_post0)
 void launch_asm_post(const PcgDev& s, const double* slots2, int it_k, int init, hipStream_t st);

@@ -1279,13 +1279,13 @@ __global__ __launch_bounds__(64, 2) void k_asm_invert(const int32_t* __restrict_
 // ASM_SYS systems of the instance share one read of the blocks.
 //   A wave of p = 4 holds 110 VGPRs of entries in flight, so two waves per SIMD
 // cover the loads and the gathers of v.  Measured (us, v = r / v = the residual
-// with its slot gather), before -> after; before, a launch per group staged
-// packed triangles through LDS behind two barriers per tile (36 KB of LDS
+// with its slot gather, RESID), before -> after; before, a launch per group
+// staged packed triangles through LDS behind two barriers per tile (36 KB of LDS
 // traffic per p = 4 element against 10 KB here), four launches on the first two:
-//   61 x 33 mesh, p = 1..4, two systems: 19-24 in all -> 7.4
-//   400 x 200 mesh, p = 1..4, three systems: 114 in all -> 81 / 122
-//   16 designs, p = 4 in the main, two systems: 245 on average -> 205
-//   160 x 80 mesh, p = 3, one system: 17.3 -> 13.2
+//   61 x 33 mesh, p = 1..4, two systems: 19-24 in all -> 6.2 / 8.4
+//   400 x 200 mesh, p = 1..4, three systems: 114 in all -> 76
+//   16 designs, p = 4 in the main, two systems: 245 on average -> 178
+//   160 x 80 mesh, p = 3, one system: 17.3 -> 11.6 / 14.7
 // (2.3-3.7 TB/s over the blocks; three waves per SIMD with the entries taken in
 // two parts spilled and lost.)  A launch of at least ASM_PERSIST blocks takes a
 // bounded grid: late in a batch most systems have stopped, and one look at 64
@@ -1312,10 +1312,9 @@ __device__ __forceinline__ uint64_t running_mask(const AsmTile& t, int l0, const
   return __ballot(lane < ASM_SYS && l < t.nsys && st == SYS_RUNNING);
 }
 
-template <int P>
+template <int P, bool RESID>
 __device__ __forceinline__ void asm_tile(const AsmTile& t, unsigned run, const double* __restrict__ v,
-                                         const PcgDev& s, double* __restrict__ out_slots, double omega, int resid,
-                                         double* lds) {
+                                         const PcgDev& s, double* __restrict__ out_slots, double omega, double* lds) {
   constexpr int G = P + 1, G2 = G * G, NE = 2 * G2, NB = 2 * G, NK = NB * (NB + 1) / 2;
   constexpr int E = asm_elems_of(P), LN = asm_lanes_of(P), K2 = (NK + 1) / 2;
   constexpr int RQ = (E * NE + 63) / 64;  // rows per lane
@@ -1351,7 +1350,7 @@ __device__ __forceinline__ void asm_tile(const AsmTile& t, unsigned run, const d
       for (int q = 0; q < RQ; ++q) {
         const int ic = max(id[q].x, 0);
         const double xv = vl[ic];
-        x[q][l] = resid ? xv - slot_sum(sl, ic, t.nfv, t.nfe) : xv;
+        x[q][l] = RESID ? xv - slot_sum(sl, ic, t.nfv, t.nfe) : xv;
       }
     }
 #pragma unroll
@@ -1402,11 +1401,10 @@ __device__ __forceinline__ void asm_tile(const AsmTile& t, unsigned run, const d
   }
 }
 
-template <int PM>
+template <int PM, bool RESID>
 __global__ __launch_bounds__(64 * ASM_WAVES, 2) void k_asm_apply(const AsmTile* __restrict__ tiles, int n_tiles,
                                                                 int xcd_run, const double* __restrict__ v, PcgDev s,
-                                                                double* __restrict__ out_slots, double omega,
-                                                                int resid) {
+                                                                double* __restrict__ out_slots, double omega) {
   __shared__ double lds[ASM_WAVES * asm_lds_of(PM)];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   double* mine = lds + wave * asm_lds_of(PM);
@@ -1421,12 +1419,12 @@ __global__ __launch_bounds__(64 * ASM_WAVES, 2) void k_asm_apply(const AsmTile* 
     const unsigned run = (unsigned)running_mask(t, 0, s);
     if (run == 0 && t.nsys <= ASM_SYS) return;
     if constexpr (PM >= 4)
-      if (t.p == 4) return asm_tile<4>(t, run, v, s, out_slots, omega, resid, mine);
+      if (t.p == 4) return asm_tile<4, RESID>(t, run, v, s, out_slots, omega, mine);
     if constexpr (PM >= 3)
-      if (t.p == 3) return asm_tile<3>(t, run, v, s, out_slots, omega, resid, mine);
+      if (t.p == 3) return asm_tile<3, RESID>(t, run, v, s, out_slots, omega, mine);
     if constexpr (PM >= 2)
-      if (t.p == 2) return asm_tile<2>(t, run, v, s, out_slots, omega, resid, mine);
-    asm_tile<1>(t, run, v, s, out_slots, omega, resid, mine);
+      if (t.p == 2) return asm_tile<2, RESID>(t, run, v, s, out_slots, omega, mine);
+    asm_tile<1, RESID>(t, run, v, s, out_slots, omega, mine);
   };
   if ((int)gridDim.x == nb) {
     const int ti = tile_at(blockIdx.x);
@@ -1446,6 +1444,16 @@ __global__ __launch_bounds__(64 * ASM_WAVES, 2) void k_asm_apply(const AsmTile* 
       run_tile(t);
     }
   }
+}
+
+// q = r - assembled slots (K z): the residual that the second application reads
+__global__ __launch_bounds__(1024) void k_asm_resid(PcgDev s) {
+  const Chunk ch = s.chunks[blockIdx.x];
+  if (!sys_running(s, ch.sys)) return;
+  const int i = ch.begin + threadIdx.x;
+  if (i >= ch.end) return;
+  const double rv = s.r[ch.dof_off + i];
+  s.q[ch.dof_off + i] = rv - slot_sum(s.slots + ch.slot_off, i, ch.nfv, ch.nfe);
 }
 
 // z = assembled slots2 (the Schwarz products)
@@ -1560,12 +1568,18 @@ void launch_asm_apply(const AsmTile* tiles, int n_tiles, int p_max, int xcd_run,
   if (n_tiles == 0) return;
   const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;
   const dim3 grid(nb >= ASM_PERSIST ? ASM_GRID : nb), block(64 * ASM_WAVES);
+  auto go = [&](auto k) {
+    hipLaunchKernelGGL(k, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega);
+  };
   switch (p_max) {
-    case 1: hipLaunchKernelGGL(k_asm_apply<1>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
-    case 2: hipLaunchKernelGGL(k_asm_apply<2>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
-    case 3: hipLaunchKernelGGL(k_asm_apply<3>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
-    default: hipLaunchKernelGGL(k_asm_apply<4>, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega, resid); break;
+    case 1: resid ? go(k_asm_apply<1, true>) : go(k_asm_apply<1, false>); break;
+    case 2: resid ? go(k_asm_apply<2, true>) : go(k_asm_apply<2, false>); break;
+    case 3: resid ? go(k_asm_apply<3, true>) : go(k_asm_apply<3, false>); break;
+    default: resid ? go(k_asm_apply<4, true>) : go(k_asm_apply<4, false>); break;
   }
+}
+void launch_asm_resid(const PcgDev& s, hipStream_t st) {
+  hipLaunchKernelGGL(k_asm_resid, dim3(s.n_chunks), dim3(1024), 0, st, s);
 }
 void launch_asm_z(const PcgDev& s, const double* slots2, hipStream_t st) {
   hipLaunchKernelGGL(k_asm_z, dim3(s.n_chunks), dim3(1024), 0, st, s, slots2);

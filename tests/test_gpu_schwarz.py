@@ -45,3 +45,14 @@ def test_bounded_grid(cuda):
     u, c, g, st = mto.Plan(pr).solve(torch.tensor(pr.rho, device=cuda))
     assert st["status"] == 0 and st["true_rel_residual"][0] <= 1e-11
     assert st["max_iterations"] < 60, st["iterations"]
+
+
+def test_residual_pass(cuda):
+    """1.1 million DOFs: the residual of the second application in a pass of
+    its own (below 2^20 DOFs the gather forms it)."""
+    from paper_1811_09821_amd import mto
+
+    pr = P.uniform_random(740, 740, 1, 1, seed=4, lo=0.4)
+    u, c, g, st = mto.Plan(pr).solve(torch.tensor(pr.rho, device=cuda))
+    assert st["status"] == 0 and st["true_rel_residual"][0] <= 1e-11
+    assert st["max_iterations"] < 60, st["iterations"]
