@@ -16,7 +16,7 @@ one plan; value = step time / 64.  The 160 x 80 uniform p = 3, d = 4
 cantilever is timed beside it as a secondary workload.
 
 Prints one JSON line (metric, value in seconds per design, roofline of the
-element-contraction kernel, the plain per-element GPU path at the same
+element product, the plain per-element GPU path at the same
 tolerance, CPU-oracle baseline on the host cores, and the launch time of the
 density filter of Sec. 2.2 and its chain rule on the same cells, of the
 QR-error indicator of Sec. 3.2.3 and the other refinement indicators and
@@ -35,16 +35,19 @@ import time
 ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
-PEAK_FP64_MFMA_TFLOPS = 78.6
+PEAK_FP64_MFMA_TFLOPS = 78.6  # matrix and vector
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "contraction_traffic.json")
-KERNEL_SRC = os.path.join(ROOT, "paper_1811_09821_amd", "csrc", "mto_kernels.hip")
+KERNEL_SRC = [os.path.join(ROOT, "paper_1811_09821_amd", "csrc", f) for f in ("mto_kernels.hip", "mto_factor.hip")]
 # tile shapes of the element contraction measured on gfx950, per (p, d, size class)
 TILE_CACHE = os.path.join(ROOT, "paper_1811_09821_amd", "tiles_gfx950.txt")
 
 
 def kernel_source_hash():
-    with open(KERNEL_SRC, "rb") as fh:
-        return hashlib.sha256(fh.read()).hexdigest()[:16]
+    h = hashlib.sha256()
+    for f in KERNEL_SRC:
+        with open(f, "rb") as fh:
+            h.update(fh.read())
+    return h.hexdigest()[:16]
 
 
 def workload(k, solid_paths=False):
@@ -268,23 +271,40 @@ def run_workload(mto, args, config, prs, path, precond, steps, warmup, tune=True
     return plan, res, rho, u
 
 
-def contraction_roofline(plan, rho, stats, config, path_name, shapes):
-    """Roofline of the dominant kernel, the element contraction (one PCG
-    product K p over all (p, d) groups): useful flops of one product over the
-    mean duration of 100 back-to-back launches between two events on the
-    plan's stream; the duration inside eagerly run PCG iterations (events on
-    each dispatch packet, a few microseconds of dispatch overhead each) is
-    reported beside it."""
+def product_flops(prs, shapes):
+    """Useful flops of one product over all systems: dense contraction, 2 d^2
+    (2 n^2)^2 per element and load case (n = p + 1), or, for the groups whose
+    product is sum-factorised (ks = -3), 2 d (16 n^3 + (2 n^2 + n) d)."""
+    factored = {tuple(int(v) for v in s.split()[:2]) for s in shapes if s.split()[3] == "-3"}
+    total = 0
+    for pr in prs:
+        for p, d in zip(pr.p, pr.d):
+            p, d = int(p), int(d)
+            n = p + 1
+            total += pr.n_load_cases * (2 * d * (16 * n**3 + (2 * n * n + n) * d) if (p, d) in factored
+                                        else 2 * d * d * (2 * n * n)**2)
+    return total
+
+
+def contraction_roofline(plan, prs, rho, stats, config, path_name, shapes):
+    """Roofline of the element product (one PCG product K p over all (p, d)
+    groups): useful flops of one product, as carried out, over the mean
+    duration of 100 back-to-back launches between two events on the plan's
+    stream; the duration inside eagerly run PCG iterations (events on each
+    dispatch packet, a few microseconds of dispatch overhead each) is reported
+    beside it, and so are the flops of the dense contraction."""
     it_min = min(stats["iterations"]) if stats else 100
     reps = max(1, min(100, it_min // 3))
     t_loop_ms = plan.time_contraction(rho, reps=reps, in_loop=True)
     t_mv_ms = plan.time_contraction(rho, reps=100)
-    flops = plan.info["flops_per_matvec"]
+    flops = product_flops(prs, shapes) if shapes else plan.info["flops_per_matvec"]
+    factored = any(s.split()[3] == "-3" for s in shapes)
     achieved = flops / (t_mv_ms * 1e-3) / 1e12
-    return {"bound": "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
+    return {"bound": "fp64 vector fma" if factored else "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_FP64_MFMA_TFLOPS, 4), "traffic": traffic_for(config, shapes, path_name),
-            "kernel": "k_elem_mfma (element contraction of every (p, d) group, PCG search direction)",
-            "flops_per_launch": flops, "ms_per_launch": round(t_mv_ms, 5), "launches_timed": 100,
+            "kernel": "k_elem_factored (sum-factorised element product, PCG search direction)" if factored else
+            "k_elem_mfma (element contraction of every (p, d) group, PCG search direction)",
+            "flops_per_launch": flops, "dense_flops_per_launch": plan.info["flops_per_matvec"], "ms_per_launch": round(t_mv_ms, 5), "launches_timed": 100,
             "ms_per_launch_in_pcg_loop": round(t_loop_ms, 5), "in_loop_reps": reps,
             "frac_in_pcg_loop": round(flops / (t_loop_ms * 1e-3) / 1e12 / PEAK_FP64_MFMA_TFLOPS, 4),
             "tile_shapes": shapes}
@@ -335,7 +355,7 @@ def contraction_only(args, prs, desc):
     report = plan.autotune(rho, cache=args.tile_cache or None)
     ms = plan.time_contraction(rho, reps=100)
     out = {"workload": desc, "ms_per_launch": ms, "tile_shapes": tile_shapes(report),
-           "flops_per_launch": plan.info["flops_per_matvec"]}
+           "flops_per_launch": product_flops(prs, tile_shapes(report))}
     if args.calibrate_copy_mb > 0:
         n = args.calibrate_copy_mb * (1 << 20) // 8
         a = torch.ones(n, dtype=torch.float64, device="cuda:0")
@@ -417,7 +437,7 @@ def main():
     progress(f"config {args.config}: {res['s_per_design']:.6f} s/design; contraction roofline")
     stats = res["stats"]
     shapes = tile_shapes(res["report"])
-    roof = contraction_roofline(plan, rho, stats, args.config, args.path, shapes)
+    roof = contraction_roofline(plan, prs, rho, stats, args.config, args.path, shapes)
     its = stats["iterations"] if stats else None
 
     out = {
@@ -471,7 +491,7 @@ def main():
         prs2, desc2 = workload(2, args.eased_field)
         plan2, res2, rho2, _ = run_workload(mto, args, 2, prs2, path, precond, max(args.steps, 20), args.warmup)
         shapes2 = tile_shapes(res2["report"])
-        roof2 = contraction_roofline(plan2, rho2, res2["stats"], 2, args.path, shapes2)
+        roof2 = contraction_roofline(plan2, prs2, rho2, res2["stats"], 2, args.path, shapes2)
         out["secondary"] = {"workload": desc2, "s_per_design": res2["s_per_design"],
                             "pcg_iterations": res2["stats"]["iterations"],
                             "true_rel_residual": res2["stats"]["true_rel_residual"],
