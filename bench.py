@@ -101,8 +101,8 @@ def cpu_baseline(prs, max_designs=16):
 def time_filter(mto, prs, rho, R, reps=200):
     """Density filter (Sec. 2.2, Eqs. (4)-(5)) and its chain rule on the same
     cells: average launch time over `reps` back-to-back launches, and the
-    HBM rate on algorithmic bytes (x, 1/rowsum and y once per cell; an index
-    and a weight per nonzero of H)."""
+    HBM rate on algorithmic bytes (x, 1/rowsum and y once per cell; one 32-bit
+    word, offset and place of the weight, per nonzero of H)."""
     import torch
 
     F = mto.Filter(prs, R)
@@ -110,7 +110,7 @@ def time_filter(mto, prs, rho, R, reps=200):
     g = F.grad(y)
     st = torch.cuda.current_stream()
     res = {"R": R, "n_cells": F.n_cells, "nnz": F.nnz}
-    nbytes = 24 * F.n_cells + 12 * F.nnz
+    nbytes = 24 * F.n_cells + 4 * F.nnz
     for name, fn, x, out in (("apply", mto.lib().mto_filter_apply, rho, y), ("grad", mto.lib().mto_filter_grad, y, g)):
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
         for _ in range(5):

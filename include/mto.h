@@ -321,8 +321,10 @@ int mto_jacobi_diagonal(mto_plan* plan, const double* rho, double* diag, void* s
 
 /* Times the element product of every (p, d) group of the plan for each
  * tile shape (ncol x ks, see mto_set_tile; the sum-factorised product
- * included) and keeps the fastest per group.  rho is a
- * representative density field.  cache_path (host string, may be NULL): a
+ * included) and keeps the fastest per group, then the whole product as
+ * chosen, as one fused contraction and with every group sum-factorised in
+ * one launch, and keeps the fastest of these.  rho is a representative
+ * density field.  cache_path (host string, may be NULL): a
  * text file of tile shapes keyed by (GPU architecture, p, d, floor(log2 of
  * the group's element columns)); a group found there takes the cached
  * shape without timing, and the shapes timed in this call are added to the

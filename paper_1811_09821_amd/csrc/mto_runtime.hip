@@ -544,9 +544,9 @@ bool read_tile_cache(const char* path, std::map<TileKey, TileChoice>& out) {
     TileChoice v;
     if (sscanf(line, "%63s %d %d %d %d %d %lf", arch, &k.p, &k.d, &k.size_class, &v.ncol, &v.ks, &v.us) != 7 ||
         (v.ncol != 1 && v.ncol != 2 && v.ncol != 4) || v.ks < -3 || v.ks == -1 || v.ks > 8 || k.p < 0 ||
-        k.p > MTO_MAX_P || (v.ks < -1 && (k.p == 0 || v.ncol != 1)) ||
+        k.p > MTO_MAX_P || (v.ks < -1 && k.p > 0 && v.ncol != 1) ||
         k.d < 0 || k.d > MTO_MAX_D * MTO_MAX_P || (k.p > 0 && k.d < 1) || (k.p > 0 && k.d > MTO_MAX_D) ||
-        (k.p > 0 && v.ks == 0 && (k.p < 3 || v.ncol == 4)) || (k.p == 0 && (v.ks != 0 || v.ncol == 4))) {
+        (k.p > 0 && v.ks == 0 && (k.p < 3 || v.ncol == 4)) || (k.p == 0 && ((v.ks != 0 && v.ks != -3) || v.ncol == 4))) {
       ok = false;
       break;
     }
@@ -563,7 +563,8 @@ bool write_tile_cache(const char* path, const std::map<TileKey, TileChoice>& c) 
   if (!fh) return false;
   fprintf(fh, "# element-contraction tile shapes: arch p d size_class(log2 columns) ncol ks us_per_launch\n"
               "# ks 0: LDS-staged tables, 64 ncol columns per tile; ks -2: stored element matrices, ks -3: sum-factorised product\n"
-              "# p 0: the plan's choice between one launch for all its d groups (ncol 1) and one per group (ncol 2)\n");
+              "# p 0: the plan's choice for its d groups: one fused contraction (ncol 1), all sum-factorised (ncol 1,\n"
+              "# ks -3) or each as chosen (ncol 2)\n");
   for (auto& kv : c)
     fprintf(fh, "%s %d %d %d %d %d %.3f\n", kv.first.arch.c_str(), kv.first.p, kv.first.d, kv.first.size_class,
             kv.second.ncol, kv.second.ks, kv.second.us);
@@ -2170,20 +2171,37 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
     cache[key] = TileChoice{best_nc, best_ks, 1e3 * best};
     changed = true;
   }
-  // one launch for all groups (the fused product) or one per group (the
-  // stored element matrices, when chosen, for these moduli)
+  // The whole product: as chosen per group (the sum-factorised groups in one
+  // launch, one more for each other group; the stored element matrices, when
+  // chosen, for these moduli), all groups contracted in one fused launch, or all
+  // sum-factorised in one launch.  A group's own time says little of what its
+  // tiles cost beside the others': 200 x 100 mesh, p = 1..4, us: 33 as chosen, 89
+  // fused, 20 all sum-factorised; 16 designs 154, 362, 140.
   enq_assemble_stored(P, st);
+  auto all_factored = [&]() {
+    P->fused = false;
+    for (auto& g : P->groups) {
+      g.factored = 1;
+      g.stored = g.lds_nc = 0;
+      g.ncol = g.waves = 1;
+    }
+  };
   {
     int64_t cols = 0;
     for (auto& g : P->groups) cols += (int64_t)(g.flops / (2.0 * g.S * g.ne * g.ne));
     const TileKey key{arch, 0, (int)P->groups.size(), size_class((double)cols)};
     auto hit = cache.find(key);
     if (hit != cache.end()) {
-      P->fused = hit->second.ncol == 1;
+      P->fused = hit->second.ncol == 1 && hit->second.ks == 0;
+      if (hit->second.ncol == 1 && hit->second.ks == -3) all_factored();
     } else {
-      double tm[2] = {0.0, 0.0};
-      for (int f = 0; f < 2; ++f) {
+      bool mixed = false;
+      for (auto& g : P->groups) mixed |= !g.factored;
+      const std::vector<GroupHost> own = P->groups;
+      double tm[3] = {0.0, 0.0, 1e300};
+      for (int f = 0; f < (mixed ? 3 : 2); ++f) {
         P->fused = f == 1;
+        if (f == 2) all_factored();
         int rc = rebuild_tiles(P);
         if (rc) return rc;
         for (int w = 0; w < 3; ++w) enq_elem_all(P, P->q, ELEM_APPLY, 0, st);
@@ -2196,12 +2214,26 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
         HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
         tm[f] = ms / reps;
       }
-      P->fused = tm[1] < tm[0];
       char line[160];
-      snprintf(line, sizeof line, "all groups: one launch per group %.3f us, one fused launch %.3f us\n", 1e3 * tm[0],
-               1e3 * tm[1]);
+      snprintf(line, sizeof line, "all groups: as chosen %.3f us, one fused launch %.3f us", 1e3 * tm[0], 1e3 * tm[1]);
       rep += line;
-      cache[key] = TileChoice{P->fused ? 1 : 2, 0, 1e3 * std::min(tm[0], tm[1])};
+      if (mixed) {
+        snprintf(line, sizeof line, ", all sum-factorised %.3f us", 1e3 * tm[2]);
+        rep += line;
+      }
+      rep += "\n";
+      const int pick = (int)(std::min_element(tm, tm + 3) - tm);
+      if (mixed && pick != 2)
+        for (size_t k = 0; k < own.size(); ++k) {
+          GroupHost& g = P->groups[k];
+          g.factored = own[k].factored;
+          g.stored = own[k].stored;
+          g.lds_nc = own[k].lds_nc;
+          g.ncol = own[k].ncol;
+          g.waves = own[k].waves;
+        }
+      P->fused = pick == 1;
+      cache[key] = TileChoice{pick == 0 ? 2 : 1, pick == 2 ? -3 : 0, 1e3 * tm[pick]};
       changed = true;
     }
   }
