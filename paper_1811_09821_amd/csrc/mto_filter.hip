@@ -72,17 +72,18 @@ __global__ __launch_bounds__(256) void k_filter(const int64_t* __restrict__ sp, 
   // consecutive blocks go to the XCDs in turn: each XCD takes a contiguous
   // eighth of the rows, whose x its L2 then holds
   const int per = gridDim.x / 8, blk = (blockIdx.x % 8) * per + blockIdx.x / 8;
+  const int64_t i = (int64_t)blk * 256 + threadIdx.x, ic = i < n ? i : n - 1;
+  const int64_t t = __builtin_amdgcn_readfirstlane((int)(ic / FSLICE));
+  const int lane = (int)(i % FSLICE);
+  // the slice's bounds and the row's scale are on their way while the table is
+  const int64_t b = sp[t];
+  const int cnt = (int)((sp[t + 1] - b) / FSLICE);  // the same for every lane
+  const double scale = GRAD ? 1.0 : s[ic];
   if (FORM == F_PACKED_LDS) {
     for (int k = threadIdx.x; k < n_tab; k += 256) tl[k] = tab[k];
     __syncthreads();
   }
-  const int64_t i = (int64_t)blk * 256 + threadIdx.x;
-  // slices past the end of the last one have no entries: sp is read only for t < n_slices
   if (i >= n) return;
-  const int64_t t = __builtin_amdgcn_readfirstlane((int)(i / FSLICE));
-  const int lane = (int)(i % FSLICE);
-  const int64_t b = sp[t];
-  const int cnt = (int)((sp[t + 1] - b) / FSLICE);  // the same for every lane
   // 32-bit byte offsets from the slice's first row less the furthest offset
   const uintptr_t x0 = (uintptr_t)x + 8 * (t * FSLICE - 32768), s0 = (uintptr_t)s + 8 * (t * FSLICE - 32768);
   double acc = 0.0;
@@ -128,7 +129,7 @@ __global__ __launch_bounds__(256) void k_filter(const int64_t* __restrict__ sp, 
     }
     k += size;
   }
-  y[i] = GRAD ? acc : s[i] * acc;
+  y[i] = GRAD ? acc : scale * acc;
 }
 
 template <class T>
