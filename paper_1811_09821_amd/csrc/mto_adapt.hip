@@ -159,12 +159,13 @@ __global__ __launch_bounds__(AD_BLOCK) void k_density_ind(AdaptDev a, const doub
   const GroupDev& G = a.groups[g];
   const int n = G.S;
   const double* __restrict__ r = rho + G.cell[k];
-  // x / n to the last bit: the quotient from the rounded reciprocal and one
-  // correction by its exact remainder
+  // x / n to the last bit: the quotient from the correctly rounded reciprocal
+  // and one correction by its exact remainder (Markstein's division).  An
+  // infinite x has no remainder and is its own quotient.
   const double dn = (double)n, rn = 1.0 / dn;
   auto over_n = [&](double x) {
     const double q = x * rn;
-    return fma(fma(-q, dn, x), rn, q);
+    return __builtin_isinf(q) ? q : fma(fma(-q, dn, x), rn, q);
   };
   double acc = 0.0;
   constexpr int BATCH = 9;  // loads in flight
