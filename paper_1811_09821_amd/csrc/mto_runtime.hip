@@ -48,6 +48,10 @@ namespace {
 
 constexpr int CHUNK = 1024;  // free DOFs per vector-kernel block (one per thread)
 constexpr int N_PROG = 4;    // PCG chunk launches in flight at most
+// The chunk graphs: iters_per_launch iterations; a short one of a quarter of
+// them (at least 2) for the last iterations before convergence; and a full
+// chunk in two parts, its head as long as a short one (see head_first).
+enum ChunkKind { CHUNK_FULL, CHUNK_SMALL, CHUNK_HEAD, CHUNK_REST, N_CHUNK };
 
 struct DevBuf {
   void* ptr = nullptr;
@@ -171,14 +175,12 @@ struct mto_plan {
   hipEvent_t ev[N_PROG] = {};
   // per-iteration decrease of log(rr / tol2) seen last (0: none yet)
   double rate_hint = 0.0;
-  bool short_first = false;  // the last solve converged within the short chunk
   hipStream_t cap_stream = nullptr;
   // the multigrid set-up runs on side_stream beside the Schwarz block inverses
   hipStream_t side_stream = nullptr;
   hipEvent_t fork_ev = nullptr, join_ev = nullptr;
   // graphs
-  hipGraphExec_t chunk_exec = nullptr, small_exec = nullptr;
-  int chunk_G = 0, small_G = 0;
+  hipGraphExec_t chunk_exec[N_CHUNK] = {};
   // bound (captured) buffers
   bool bound = false;
   const double* b_rho = nullptr;
@@ -299,7 +301,8 @@ int dev_upload(mto_plan* P, T** out, const std::vector<T>& h) {
 }
 
 void destroy_graphs(mto_plan* P) {
-  hipGraphExec_t* gs[] = {&P->chunk_exec, &P->small_exec, &P->setup_exec, &P->resid_exec, &P->restart_exec, &P->out_exec};
+  std::vector<hipGraphExec_t*> gs = {&P->setup_exec, &P->resid_exec, &P->restart_exec, &P->out_exec};
+  for (auto& c : P->chunk_exec) gs.push_back(&c);
   for (auto g : gs)
     if (*g) {
       (void)hipGraphExecDestroy(*g);
@@ -1319,10 +1322,10 @@ void enq_setup(mto_plan* P, const double* rho, const double* u0, hipStream_t st)
   }
 }
 
-// G PCG iterations; the last one checks for residual replacement (systems
-// whose recursive residual has come near its rounding floor) before its
-// V-cycle, which then forms z from the replaced residual.
-void enq_chunk(mto_plan* P, int G, hipStream_t st) {
+// G PCG iterations; the last one (replace) checks for residual replacement
+// (systems whose recursive residual has come near its rounding floor) before
+// its V-cycle, which then forms z from the replaced residual.
+void enq_chunk(mto_plan* P, int G, bool replace, hipStream_t st) {
   const PcgDev s = P->pcg();
   std::vector<GroupDev> gd;
   for (auto& g : P->groups) gd.push_back(P->gdev(g));
@@ -1330,7 +1333,7 @@ void enq_chunk(mto_plan* P, int G, hipStream_t st) {
     enq_elem_all(P, P->p, ELEM_PCG, k, st);
     launch_dof1(s, k, st);
     launch_dof2(s, k, st);
-    if (k == G - 1)
+    if (replace && k == G - 1)
       launch_replace(gd.data(), (int)gd.size(), P->d_tiles, P->E, s, P->xs_hi, P->xs_lo, P->slots_lo, k, st);
     if (P->prm.precond != MTO_PRECOND_JACOBI) enq_vcycle(P, k, 0, st);
   }
@@ -1390,18 +1393,26 @@ int capture(mto_plan* P, hipGraphExec_t* exec, const std::function<void(hipStrea
   return MTO_OK;
 }
 
-// The chunk graphs: G iterations, and a short one of max(2, G / 4) for the
-// last iterations before convergence (both even: the parity of it_base).
-int ensure_chunk_graph(mto_plan* P) {
-  const int G = P->prm.iters_per_launch;
-  if (P->chunk_exec && P->small_exec && P->chunk_G == G) return MTO_OK;
-  const int Gs = std::max(2, (G / 4) & ~1);
-  int rc = capture(P, &P->chunk_exec, [&](hipStream_t st) { enq_chunk(P, G, st); });
-  if (rc) return rc;
-  if ((rc = capture(P, &P->small_exec, [&](hipStream_t st) { enq_chunk(P, Gs, st); }))) return rc;
-  P->chunk_G = G;
-  P->small_G = Gs;
-  return MTO_OK;
+// Iterations of each kind of chunk (all even: the parity of it_base).
+int chunk_len(const mto_plan* P, ChunkKind kind) {
+  const int G = P->prm.iters_per_launch, Gs = std::max(2, (G / 4) & ~1);
+  return kind == CHUNK_FULL ? G : kind == CHUNK_REST ? G - Gs : Gs;
+}
+
+// Whether a solve's first full chunk goes as its head alone, then its rest.
+// One V-cycle is the exact inverse, and a solve over in one or two iterations,
+// where the level below the elements is all of the space (p = 1), is the
+// coarsest one, solved directly, and is all of the operator (no ground springs).
+bool head_first(const mto_plan* P) {
+  bool exact = P->prm.precond != MTO_PRECOND_JACOBI && P->mg.L == 1 && !P->kspr;
+  for (auto& g : P->groups) exact &= g.p == 1;
+  return exact && chunk_len(P, CHUNK_REST) > 0;
+}
+
+int chunk_graph(mto_plan* P, ChunkKind kind) {
+  if (P->chunk_exec[kind]) return MTO_OK;
+  return capture(P, &P->chunk_exec[kind],
+                 [&](hipStream_t st) { enq_chunk(P, chunk_len(P, kind), kind != CHUNK_HEAD, st); });
 }
 
 // Runs PCG iterations until every system has stopped or the cap is reached.
@@ -1413,9 +1424,10 @@ int ensure_chunk_graph(mto_plan* P) {
 // system has stopped (those return at once but still cost their launches).
 // r0 is rr / tol2 at iteration 0 when the caller knows it (else <= 0).
 int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
-  int rc = ensure_chunk_graph(P);
-  if (rc) return rc;
-  const int G = P->chunk_G, Gs = P->small_G;
+  int rc;
+  const int G = chunk_len(P, CHUNK_FULL);
+  const bool head = head_first(P);  // its plans seldom need more than the head: the others when they are launched
+  if (!head && ((rc = chunk_graph(P, CHUNK_FULL)) || (rc = chunk_graph(P, CHUNK_SMALL)))) return rc;
   int64_t cap = P->prm.max_iter;
   if (cap <= 0) {
     int64_t mx = 0;
@@ -1427,19 +1439,20 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
     int64_t end;
   };
   Pending pend[N_PROG];
-  int head = 0, n_pend = 0, next_slot = 0;
+  int head_at = 0, n_pend = 0, next_slot = 0;
   int64_t queued = 0, known = 0;
   // reports (iteration, rr / tol2) of this cycle while systems still run
   std::vector<std::pair<int64_t, double>> hist;
   if (r0 > 1.0 && std::isfinite(r0)) hist.emplace_back(0, r0);
-  auto launch = [&](bool full) -> int {
+  auto launch = [&](ChunkKind kind) -> int {
+    if ((rc = chunk_graph(P, kind))) return rc;
     const int slot = next_slot;
     next_slot = (next_slot + 1) % N_PROG;
-    HIP_TRY(hipGraphLaunch(full ? P->chunk_exec : P->small_exec, st));
+    HIP_TRY(hipGraphLaunch(P->chunk_exec[kind], st));
     HIP_TRY(hipMemcpyAsync(P->h_prog + 2 * slot, P->progress, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(P->ev[slot], st));
-    queued += full ? G : Gs;
-    pend[(head + n_pend) % N_PROG] = Pending{slot, queued};
+    queued += chunk_len(P, kind);
+    pend[(head_at + n_pend) % N_PROG] = Pending{slot, queued};
     ++n_pend;
     return MTO_OK;
   };
@@ -1458,18 +1471,29 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
       const double need = std::ceil(std::log(hist.back().second) / rate);  // >= 1: the ratio is > 1
       if (need < double(cap)) target = std::min(target, hist.back().first + (int64_t)need);
     }
-    // The plan's last solve was over within the short chunk: that one alone
-    // first.  The 14 further iterations would pass through the device unused (20 x
-    // 10 mesh, one iteration: a solve takes 0.40 ms, 0.69 with them).  Nothing
-    // else changes where chunks end, so the bits do not either.
-    if (known == 0 && P->short_first) target = Gs;
     if (queued < target && queued < cap && n_pend < N_PROG) {
-      if ((rc = launch(target - queued >= G))) return rc;
+      const bool full = target - queued >= G;
+      // The head of the first full chunk alone, then, if it was not enough, the
+      // rest: the 14 further iterations would pass through the device unused (20 x
+      // 10 mesh, one iteration: a solve takes 0.40 ms, 0.69 with them).  The head
+      // replaces no residual and its report enters no estimate, so everything
+      // after it is as with the chunk in one piece, to the bit.
+      if (full && head && queued == 0) {
+        if ((rc = launch(CHUNK_HEAD))) return rc;
+        const Pending pd = pend[head_at];
+        head_at = (head_at + 1) % N_PROG;
+        --n_pend;
+        HIP_TRY(hipEventSynchronize(P->ev[pd.slot]));
+        if (P->h_prog[2 * pd.slot] == 0.0) break;
+        if ((rc = launch(CHUNK_REST))) return rc;
+      } else if ((rc = launch(full ? CHUNK_FULL : CHUNK_SMALL))) {
+        return rc;
+      }
       continue;
     }
     if (n_pend == 0) break;  // the cap is reached
-    const Pending pd = pend[head];
-    head = (head + 1) % N_PROG;
+    const Pending pd = pend[head_at];
+    head_at = (head_at + 1) % N_PROG;
     --n_pend;
     HIP_TRY(hipEventSynchronize(P->ev[pd.slot]));
     known = pd.end;
@@ -1534,10 +1558,8 @@ int run_solve(mto_plan* P, const double* rho, double* u, double* c, double* g, c
     }
     if ((rc = fetch(P, st, R))) return rc;
     bool any_breakdown = false, any_running = false, need_restart = false, any_bad = false;
-    if (restarts == 0) P->short_first = true;
     for (int s = 0; s < P->n_sys; ++s) {
       iters_total[s] += R.iters[s];
-      if (R.status[s] != SYS_CONVERGED || R.iters[s] > P->small_G) P->short_first = false;
       if (R.status[s] == SYS_BREAKDOWN) any_breakdown = true;
       else if (R.status[s] == SYS_RUNNING) any_running = true;
       else if (R.status[s] == SYS_BADINPUT) any_bad = true;
@@ -1678,7 +1700,8 @@ int mto_batch_capture(mto_plan* P, const double* rho, double* u, double* c, doub
   if ((rc = capture(P, &P->resid_exec, [&](hipStream_t st) { enq_cycle_end(P, st); }))) return rc;
   if ((rc = capture(P, &P->restart_exec, [&](hipStream_t st) { enq_restart(P, st); }))) return rc;
   if ((rc = capture(P, &P->out_exec, [&](hipStream_t st) { enq_outputs(P, u, c, g, st); }))) return rc;
-  if ((rc = ensure_chunk_graph(P))) return rc;
+  for (int k = 0; k < N_CHUNK; ++k)
+    if ((k == CHUNK_FULL || k == CHUNK_SMALL || head_first(P)) && (rc = chunk_graph(P, (ChunkKind)k))) return rc;
   P->bound = true;
   P->b_rho = rho;
   P->b_u = u;
