@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <deque>
 #include <functional>
 #include <map>
 #include <mutex>
@@ -48,10 +49,10 @@ namespace {
 
 constexpr int CHUNK = 1024;  // free DOFs per vector-kernel block (one per thread)
 constexpr int N_PROG = 4;    // PCG chunk launches in flight at most
-// The chunk graphs: iters_per_launch iterations; a short one of a quarter of
-// them (at least 2) for the last iterations before convergence; and a full
-// chunk in two parts, its head as long as a short one (see head_first).
-enum ChunkKind { CHUNK_FULL, CHUNK_SMALL, CHUNK_HEAD, CHUNK_REST, N_CHUNK };
+// The chunk graphs: iters_per_launch iterations; a short chunk of a quarter of
+// them (at least 2) for the last iterations before convergence; and a part of
+// a full chunk, as long as a short one but without residual replacement.
+enum ChunkKind { CHUNK_FULL, CHUNK_SMALL, CHUNK_PART, N_CHUNK };
 
 struct DevBuf {
   void* ptr = nullptr;
@@ -173,7 +174,8 @@ struct mto_plan {
   // host pinned: one progress report per chunk launch in flight
   double* h_prog = nullptr;  // [N_PROG][2]
   hipEvent_t ev[N_PROG] = {};
-  // per-iteration decrease of log(rr / tol2) seen last (0: none yet)
+  // per-iteration decrease of log(rr / tol2) seen last (0: none yet): how much
+  // of a solve to launch ahead, nothing that its results depend on
   double rate_hint = 0.0;
   hipStream_t cap_stream = nullptr;
   // the multigrid set-up runs on side_stream beside the Schwarz block inverses
@@ -1395,39 +1397,46 @@ int capture(mto_plan* P, hipGraphExec_t* exec, const std::function<void(hipStrea
 
 // Iterations of each kind of chunk (all even: the parity of it_base).
 int chunk_len(const mto_plan* P, ChunkKind kind) {
-  const int G = P->prm.iters_per_launch, Gs = std::max(2, (G / 4) & ~1);
-  return kind == CHUNK_FULL ? G : kind == CHUNK_REST ? G - Gs : Gs;
-}
-
-// Whether a solve's first full chunk goes as its head alone, then its rest.
-// One V-cycle is the exact inverse, and a solve over in one or two iterations,
-// where the level below the elements is all of the space (p = 1), is the
-// coarsest one, solved directly, and is all of the operator (no ground springs).
-bool head_first(const mto_plan* P) {
-  bool exact = P->prm.precond != MTO_PRECOND_JACOBI && P->mg.L == 1 && !P->kspr;
-  for (auto& g : P->groups) exact &= g.p == 1;
-  return exact && chunk_len(P, CHUNK_REST) > 0;
+  const int G = P->prm.iters_per_launch;
+  return kind == CHUNK_FULL ? G : std::max(2, (G / 4) & ~1);
 }
 
 int chunk_graph(mto_plan* P, ChunkKind kind) {
   if (P->chunk_exec[kind]) return MTO_OK;
   return capture(P, &P->chunk_exec[kind],
-                 [&](hipStream_t st) { enq_chunk(P, chunk_len(P, kind), kind != CHUNK_HEAD, st); });
+                 [&](hipStream_t st) { enq_chunk(P, chunk_len(P, kind), kind != CHUNK_PART, st); });
+}
+
+// Whether one V-cycle is the exact inverse, and a solve over in an iteration or
+// two: the level below the elements is all of the space (p = 1), is the coarsest
+// one, solved directly, and is all of the operator (no ground springs).
+bool exact_vcycle(const mto_plan* P) {
+  bool exact = P->prm.precond != MTO_PRECOND_JACOBI && P->mg.L == 1 && !P->kspr;
+  for (auto& g : P->groups) exact &= g.p == 1;
+  return exact;
 }
 
 // Runs PCG iterations until every system has stopped or the cap is reached.
 // Each chunk ends by reporting the number of running systems and the largest
-// rr / tol2 among them.  The host keeps at most two full chunks queued past
-// the last report, as a plain pipeline would, but no more iterations than
-// the log-linear extrapolation of that ratio to 1 asks for; near the end it
-// queues short chunks, so that few iterations are launched after the last
-// system has stopped (those return at once but still cost their launches).
-// r0 is rr / tol2 at iteration 0 when the caller knows it (else <= 0).
-int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
+// rr / tol2 among them.  At most two full chunks are planned past the last
+// chunk whose report is in, as a plain pipeline would have it, but no more
+// iterations than the log-linear extrapolation of that ratio to 1 asks for;
+// near the end the chunks are short, so that few iterations are launched after
+// the last system has stopped (those return at once but still cost their
+// launches).  r0 is rr / tol2 at iteration 0 when the caller knows it (else <= 0),
+// cycle_rate the rate of decrease in this solve's previous cycle (0: none).
+//   Residuals are replaced where chunks end, so the chunks follow from this solve
+// alone: with them the results would depend on what the plan solved before.
+// What it solved before (rate_hint), or its structure, only tells how much of
+// the planned chunks is worth launching yet: a full chunk within which the solve
+// is expected to end goes in parts, which replace nothing and whose reports plan
+// nothing.  20 x 10 mesh, one iteration: a solve takes 0.40 ms, 0.69 with two
+// full chunks queued.
+int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0, double& cycle_rate) {
   int rc;
-  const int G = chunk_len(P, CHUNK_FULL);
-  const bool head = head_first(P);  // its plans seldom need more than the head: the others when they are launched
-  if (!head && ((rc = chunk_graph(P, CHUNK_FULL)) || (rc = chunk_graph(P, CHUNK_SMALL)))) return rc;
+  const int G = chunk_len(P, CHUNK_FULL), Gs = chunk_len(P, CHUNK_SMALL);
+  const bool exact = exact_vcycle(P);  // seldom needs more than a part: the other graphs when they are launched
+  if (!exact && ((rc = chunk_graph(P, CHUNK_FULL)) || (rc = chunk_graph(P, CHUNK_SMALL)))) return rc;
   int64_t cap = P->prm.max_iter;
   if (cap <= 0) {
     int64_t mx = 0;
@@ -1439,11 +1448,40 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
     int64_t end;
   };
   Pending pend[N_PROG];
-  int head_at = 0, n_pend = 0, next_slot = 0;
-  int64_t queued = 0, known = 0;
-  // reports (iteration, rr / tol2) of this cycle while systems still run
-  std::vector<std::pair<int64_t, double>> hist;
-  if (r0 > 1.0 && std::isfinite(r0)) hist.emplace_back(0, r0);
+  int head = 0, n_pend = 0, next_slot = 0;
+  int64_t queued = 0, reported = 0;
+  struct PlannedChunk {
+    int64_t end;
+    bool full;
+  };
+  std::deque<PlannedChunk> chunks;        // not launched to their end yet
+  std::deque<int64_t> ends;               // of the chunks without a report
+  int64_t planned = 0, known = 0;         // end of the last chunk; of the last one with a report
+  // reports (iteration, rr / tol2) of this cycle while systems still run: those
+  // at the ends of chunks, and all
+  std::vector<std::pair<int64_t, double>> hist, seen;
+  if (r0 > 1.0 && std::isfinite(r0)) {
+    hist.emplace_back(0, r0);
+    seen = hist;
+  }
+  // the iteration, at most `limit`, at which reports h expect the ratio to reach
+  // 1, by their rate or, where they are too few, `fallback` (0: unknown)
+  auto expected_end = [&](const std::vector<std::pair<int64_t, double>>& h, double fallback, int64_t limit,
+                          double& rate) {
+    rate = 0.0;
+    if (h.size() >= 2) {
+      // the latest report against the newest one at least G iterations older
+      size_t j = h.size() - 2;
+      while (j > 0 && h.back().first - h[j].first < G) --j;
+      rate = std::log(h[j].second / h.back().second) / double(h.back().first - h[j].first);
+    }
+    if (!(rate > 0.0 && std::isfinite(rate))) rate = fallback;
+    if (rate > 0.0 && !h.empty()) {
+      const double need = std::ceil(std::log(h.back().second) / rate);  // >= 1: the ratio is > 1
+      if (need < double(cap)) limit = std::min(limit, h.back().first + (int64_t)need);
+    }
+    return limit;
+  };
   auto launch = [&](ChunkKind kind) -> int {
     if ((rc = chunk_graph(P, kind))) return rc;
     const int slot = next_slot;
@@ -1452,56 +1490,50 @@ int iterate(mto_plan* P, hipStream_t st, int64_t& launched, double r0) {
     HIP_TRY(hipMemcpyAsync(P->h_prog + 2 * slot, P->progress, 2 * sizeof(double), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipEventRecord(P->ev[slot], st));
     queued += chunk_len(P, kind);
-    pend[(head_at + n_pend) % N_PROG] = Pending{slot, queued};
+    pend[(head + n_pend) % N_PROG] = Pending{slot, queued};
     ++n_pend;
     return MTO_OK;
   };
   double rate = 0.0;
   while (true) {
-    int64_t target = known + 2 * G;
-    rate = 0.0;
-    if (hist.size() >= 2) {
-      // the latest report against the newest one at least G iterations older
-      size_t j = hist.size() - 2;
-      while (j > 0 && hist.back().first - hist[j].first < G) --j;
-      rate = std::log(hist[j].second / hist.back().second) / double(hist.back().first - hist[j].first);
-    }
-    if (!(rate > 0.0 && std::isfinite(rate))) rate = P->rate_hint;
-    if (rate > 0.0 && !hist.empty()) {
-      const double need = std::ceil(std::log(hist.back().second) / rate);  // >= 1: the ratio is > 1
-      if (need < double(cap)) target = std::min(target, hist.back().first + (int64_t)need);
-    }
-    if (queued < target && queued < cap && n_pend < N_PROG) {
-      const bool full = target - queued >= G;
-      // The head of the first full chunk alone, then, if it was not enough, the
-      // rest: the 14 further iterations would pass through the device unused (20 x
-      // 10 mesh, one iteration: a solve takes 0.40 ms, 0.69 with them).  The head
-      // replaces no residual and its report enters no estimate, so everything
-      // after it is as with the chunk in one piece, to the bit.
-      if (full && head && queued == 0) {
-        if ((rc = launch(CHUNK_HEAD))) return rc;
-        const Pending pd = pend[head_at];
-        head_at = (head_at + 1) % N_PROG;
-        --n_pend;
-        HIP_TRY(hipEventSynchronize(P->ev[pd.slot]));
-        if (P->h_prog[2 * pd.slot] == 0.0) break;
-        if ((rc = launch(CHUNK_REST))) return rc;
-      } else if ((rc = launch(full ? CHUNK_FULL : CHUNK_SMALL))) {
-        return rc;
-      }
+    const int64_t target = expected_end(hist, cycle_rate, known + 2 * G, rate);
+    if (planned < target && planned < cap && ends.size() < N_PROG) {
+      const bool full = target - planned >= G;
+      planned += full ? G : Gs;
+      chunks.push_back(PlannedChunk{planned, full});
+      ends.push_back(planned);
       continue;
     }
+    if (!chunks.empty() && n_pend < N_PROG) {
+      double r;
+      int64_t until = expected_end(seen, P->rate_hint, planned, r);
+      if (exact && reported < Gs) until = std::min<int64_t>(until, Gs);
+      if (queued < until || n_pend == 0) {
+        const PlannedChunk c = chunks.front();
+        const bool whole = c.full && queued == c.end - G && (until >= c.end || G % Gs != 0);
+        const bool last = !c.full || queued + Gs == c.end;  // replaces residuals
+        if ((rc = launch(whole ? CHUNK_FULL : last ? CHUNK_SMALL : CHUNK_PART))) return rc;
+        if (queued == c.end) chunks.pop_front();
+        continue;
+      }
+    }
     if (n_pend == 0) break;  // the cap is reached
-    const Pending pd = pend[head_at];
-    head_at = (head_at + 1) % N_PROG;
+    const Pending pd = pend[head];
+    head = (head + 1) % N_PROG;
     --n_pend;
     HIP_TRY(hipEventSynchronize(P->ev[pd.slot]));
-    known = pd.end;
+    reported = pd.end;
     const double running = P->h_prog[2 * pd.slot], far = P->h_prog[2 * pd.slot + 1];
     if (running == 0.0) break;
-    if (far > 1.0 && std::isfinite(far)) hist.emplace_back(pd.end, far);
+    const bool valid = far > 1.0 && std::isfinite(far);
+    if (valid) seen.emplace_back(pd.end, far);
+    if (pd.end == ends.front()) {
+      ends.pop_front();
+      known = pd.end;
+      if (valid) hist.emplace_back(pd.end, far);
+    }
   }
-  if (rate > 0.0 && std::isfinite(rate)) P->rate_hint = rate;
+  if (rate > 0.0 && std::isfinite(rate)) P->rate_hint = cycle_rate = rate;
   launched = queued;
   // no synchronisation here: the caller's next work (the true residual and
   // its copy to the host) follows these chunks in stream order
@@ -1546,10 +1578,10 @@ int run_solve(mto_plan* P, const double* rho, double* u, double* c, double* g, c
   // rr / tol2 at the start of a cycle: 1 / rtol^2 from x = 0, else from the
   // true residuals of the last cycle (unknown for a given initial guess)
   const double rtol2 = P->prm.rtol * P->prm.rtol;
-  double r0 = u0 ? 0.0 : 1.0 / rtol2;
+  double r0 = u0 ? 0.0 : 1.0 / rtol2, cycle_rate = 0.0;
   while (true) {
     int64_t launched = 0;
-    if ((rc = iterate(P, st, launched, r0))) return rc;
+    if ((rc = iterate(P, st, launched, r0, cycle_rate))) return rc;
     if (graphs) {
       HIP_TRY(hipGraphLaunch(P->resid_exec, st));
     } else {
@@ -1700,8 +1732,8 @@ int mto_batch_capture(mto_plan* P, const double* rho, double* u, double* c, doub
   if ((rc = capture(P, &P->resid_exec, [&](hipStream_t st) { enq_cycle_end(P, st); }))) return rc;
   if ((rc = capture(P, &P->restart_exec, [&](hipStream_t st) { enq_restart(P, st); }))) return rc;
   if ((rc = capture(P, &P->out_exec, [&](hipStream_t st) { enq_outputs(P, u, c, g, st); }))) return rc;
-  for (int k = 0; k < N_CHUNK; ++k)
-    if ((k == CHUNK_FULL || k == CHUNK_SMALL || head_first(P)) && (rc = chunk_graph(P, (ChunkKind)k))) return rc;
+  if ((rc = chunk_graph(P, CHUNK_FULL)) || (rc = chunk_graph(P, CHUNK_SMALL))) return rc;
+  if (exact_vcycle(P) && (rc = chunk_graph(P, CHUNK_PART))) return rc;
   P->bound = true;
   P->b_rho = rho;
   P->b_u = u;

@@ -2,8 +2,9 @@
 move the iterations at which residuals are replaced, the bits of the results
 or the iteration cap.
 
-Plans of first-order elements on a mesh that is itself the coarsest grid take
-their first chunk in two parts; the others do not.
+A full chunk within which the solve is expected to end (by the rate of an
+earlier solve, or because the plan's V-cycle is the exact inverse) goes in
+parts, the others whole.
 """
 
 import numpy as np
@@ -24,6 +25,9 @@ CASES = {
     "mbb": (P.mbb_20x10, {}),
     "plain_40x20_p1d2": (lambda: P.cantilever_uniform(40, 20, 1, 2, sigma=3.0, seed=3, solid_paths=False),
                          dict(rtol=1e-13)),
+    # ends within the second chunk of its last cycle
+    "plain_61x33_p1d5_restart": (lambda: P.cantilever_uniform(61, 33, 1, 5, sigma=3.0, seed=2, solid_paths=False), {}),
+    "plain_61x33_p1d5": (lambda: P.cantilever_uniform(61, 33, 1, 5, sigma=3.0, seed=8, solid_paths=False), {}),
     "p1_coarsened": (lambda: P.uniform_random(61, 33, 1, 1, seed=4), {}),
 }
 
@@ -40,8 +44,8 @@ def same(a, b):
 
 @pytest.mark.parametrize("key", sorted(CASES))
 def test_solve_after_a_warm_start(cuda, key):
-    """Cold, warm from its result (no or few iterations), cold: the third
-    equals the first and the first solve of a new plan, bit for bit."""
+    """Cold twice, warm from the result (no or few iterations), cold, replayed:
+    the cold ones equal each other and a new plan's first, bit for bit."""
     make, kw = CASES[key]
     pr = make()
     rho = torch.tensor(pr.rho, device=cuda)
@@ -52,12 +56,15 @@ def test_solve_after_a_warm_start(cuda, key):
 
     plan = mto().Plan(pr, **kw)
     first = cold(plan)
+    assert same(cold(plan), first)
     warm = plan.solve(rho, u0=first[0], allow_noconv=True)
     assert max(warm[3]["iterations"]) <= max(first[3]["iterations"])
     assert same(cold(plan), first)
     assert same(cold(mto().Plan(pr, **kw)), first)
-    plan.capture(rho)
-    plan.replay()
+    u, c, g = plan.capture(rho)
+    for _ in range(2):
+        st = plan.replay(allow_noconv=True)
+        assert same((u, c, g, st), first)
     assert same(cold(plan), first)
 
 
@@ -72,12 +79,12 @@ def test_iteration_cap_after_a_warm_start(cuda, key):
     assert its[0] == its[2] <= 8 and its[1] <= 2, its
 
 
-@pytest.mark.parametrize("iters_per_launch", [2, 4, 8, 16])
+@pytest.mark.parametrize("iters_per_launch", [2, 4, 8, 16, 28])
 @pytest.mark.parametrize("rtol", [1e-11, 1e-13])
-def test_first_chunk_in_two_parts(cuda, iters_per_launch, rtol):
-    """The first chunk's head and rest at every chunk length against the
-    oracle (u and c to 1e-8, dc/drho to 1e-7, as for the other solves); at 2
-    the chunk is not divided."""
+def test_chunk_in_parts(cuda, iters_per_launch, rtol):
+    """The first chunk in parts at several lengths (28 is not a whole number of
+    parts) against the oracle (u and c to 1e-8, dc/drho to 1e-7, as for the
+    other solves)."""
     pr = CASES["plain_40x20_p1d2"][0]()
     u, c, g, st = mto().Plan(pr, iters_per_launch=iters_per_launch, rtol=rtol).solve(
         torch.tensor(pr.rho, device=cuda))
