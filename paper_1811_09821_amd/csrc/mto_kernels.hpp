@@ -369,6 +369,8 @@ struct AsmTile {
   int32_t n_free, nfv, nfe;
   int32_t count, sys, nsys, p, pad;
 };
+// Blocks of launch_asm_apply (see mto_mg.hip).
+int asm_apply_blocks(int n_tiles);
 // slots2 = omega * B_e v_e for the running systems of the tiles (any group;
 // p_max: their largest order), v_e gathered from v, or (resid) from v -
 // assembled slots

@@ -18,6 +18,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 #include <type_traits>
 
 #include "mto_kernels.hpp"
@@ -1575,11 +1576,24 @@ void launch_asm_block(const GroupDev& g, int gi, const GroupDev* groups, const i
   }
 }
 
+// One block per ASM_WAVES tiles, or the bounded grid.  MTO_ASM_GRID (a positive
+// integer) caps the count: the results do not depend on it (every tile is
+// summed the same way by whichever wave takes it), which lets tests walk the
+// tiles of small meshes as the bounded grid walks those of large ones.
+int asm_apply_blocks(int n_tiles) {
+  const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;
+  int blocks = nb >= ASM_PERSIST ? ASM_GRID : nb;
+  if (const char* cap = std::getenv("MTO_ASM_GRID")) {
+    const int c = std::atoi(cap);
+    if (c > 0) blocks = std::min(blocks, c);
+  }
+  return blocks;
+}
+
 void launch_asm_apply(const AsmTile* tiles, int n_tiles, int p_max, int xcd_run, const double* v, int resid,
                       const PcgDev& s, double* slots2, double omega, hipStream_t st) {
   if (n_tiles == 0) return;
-  const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;
-  const dim3 grid(nb >= ASM_PERSIST ? ASM_GRID : nb), block(64 * ASM_WAVES);
+  const dim3 grid(asm_apply_blocks(n_tiles)), block(64 * ASM_WAVES);
   auto go = [&](auto k) {
     hipLaunchKernelGGL(k, grid, block, 0, st, tiles, n_tiles, xcd_run, v, s, slots2, omega);
   };
