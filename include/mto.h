@@ -326,9 +326,12 @@ int mto_jacobi_diagonal(mto_plan* plan, const double* rho, double* diag, void* s
  * one launch, and keeps the fastest of these.  rho is a representative
  * density field.  cache_path (host string, may be NULL): a
  * text file of tile shapes keyed by (GPU architecture, p, d, floor(log2 of
- * the group's element columns)); a group found there takes the cached
- * shape without timing, and the shapes timed in this call are added to the
- * file (a missing file is created; MTO_EINVAL if it cannot be parsed).
+ * the group's element columns)), and of whole-product choices keyed by the
+ * plan's set of such groups; a group or plan found there takes the cached
+ * choice without timing, and the choices timed in this call are added to the
+ * file (a missing file is created; MTO_EINVAL if it cannot be parsed).  Each
+ * line names the set of candidates it was chosen among; lines without one, or
+ * with another, as files of earlier versions have, are timed anew and replaced.
  * report (host, may be NULL) receives a text summary of at most report_len
  * bytes.  With mto_params.stored_matrices = 1 the stored element matrices
  * (mto_set_tile ks = -2) are a candidate for the groups of p >= 3.  Blocks

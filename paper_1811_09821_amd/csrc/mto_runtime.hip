@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <chrono>
 #include <cmath>
 #include <cstdio>
@@ -14,6 +15,7 @@
 #include <map>
 #include <mutex>
 #include <string>
+#include <tuple>
 #include <vector>
 
 #include "mto_internal.hpp"
@@ -499,17 +501,21 @@ int rebuild_tiles(mto_plan* P) {
 }
 
 // ---- autotune cache: one text line per (arch, p, d, size class) ----
-// "arch p d size_class ncol ks us"; size class = floor(log2(element columns
+// "arch p d size_class ncol ks us set"; size class = floor(log2(element columns
 // of the group)), since the best tile shape of a group of a few elements and
-// of a full mesh differ.
+// of a full mesh differ.  The choice for a whole plan has p = 0, the number of
+// groups for d, the class of all columns and, last, the groups it was measured
+// on, "p.d.class" each: it says nothing of a plan of other groups.  set: the
+// candidates that were timed (TILE_SET); a line without it, or of another set, may
+// name a kernel that is not the fastest any more and is left out of what is read.
+constexpr int TILE_SET = 2;  // 2: with the sum-factorised product (ks = -3)
+constexpr int TILE_GROUPS_LEN = 511;
 struct TileKey {
   std::string arch;
   int p, d, size_class;
+  std::string groups;  // p = 0
   bool operator<(const TileKey& o) const {
-    if (arch != o.arch) return arch < o.arch;
-    if (p != o.p) return p < o.p;
-    if (d != o.d) return d < o.d;
-    return size_class < o.size_class;
+    return std::tie(arch, p, d, size_class, groups) < std::tie(o.arch, o.p, o.d, o.size_class, o.groups);
   }
 };
 struct TileChoice {
@@ -526,8 +532,8 @@ int size_class(double columns) {
   return c;
 }
 
-// Reads the cache if the file exists (a missing file is an empty cache);
-// false on a malformed line.
+// Reads the cache if the file exists (a missing file is an empty cache),
+// without the lines of another candidate set; false on a malformed line.
 bool read_tile_cache(const char* path, std::map<TileKey, TileChoice>& out) {
   FILE* fh = fopen(path, "r");
   if (!fh) return true;
@@ -544,10 +550,13 @@ bool read_tile_cache(const char* path, std::map<TileKey, TileChoice>& out) {
       break;
     }
     if (line[0] == '#' || line[0] == '\n') continue;
-    char arch[64];
+    char arch[64], groups[TILE_GROUPS_LEN + 1] = "";
+    int set = 0;
     TileKey k;
     TileChoice v;
-    if (sscanf(line, "%63s %d %d %d %d %d %lf", arch, &k.p, &k.d, &k.size_class, &v.ncol, &v.ks, &v.us) != 7 ||
+    static_assert(TILE_GROUPS_LEN == 511, "the width in the format");
+    if (sscanf(line, "%63s %d %d %d %d %d %lf %d %511s", arch, &k.p, &k.d, &k.size_class, &v.ncol, &v.ks, &v.us, &set,
+               groups) < 7 ||
         (v.ncol != 1 && v.ncol != 2 && v.ncol != 4) || v.ks < -3 || v.ks == -1 || v.ks > 8 || k.p < 0 ||
         k.p > MTO_MAX_P || (v.ks < -1 && k.p > 0 && v.ncol != 1) ||
         k.d < 0 || k.d > MTO_MAX_D * MTO_MAX_P || (k.p > 0 && k.d < 1) || (k.p > 0 && k.d > MTO_MAX_D) ||
@@ -555,7 +564,9 @@ bool read_tile_cache(const char* path, std::map<TileKey, TileChoice>& out) {
       ok = false;
       break;
     }
+    if (set != TILE_SET) continue;
     k.arch = arch;
+    if (k.p == 0) k.groups = groups;
     out[k] = v;
   }
   fclose(fh);
@@ -566,13 +577,13 @@ bool write_tile_cache(const char* path, const std::map<TileKey, TileChoice>& c) 
   const std::string tmp = std::string(path) + ".tmp";
   FILE* fh = fopen(tmp.c_str(), "w");
   if (!fh) return false;
-  fprintf(fh, "# element-contraction tile shapes: arch p d size_class(log2 columns) ncol ks us_per_launch\n"
+  fprintf(fh, "# element-product tile shapes: arch p d size_class(log2 columns) ncol ks us_per_launch candidate_set\n"
               "# ks 0: LDS-staged tables, 64 ncol columns per tile; ks -2: stored element matrices, ks -3: sum-factorised product\n"
               "# p 0: the plan's choice for its d groups: one fused contraction (ncol 1), all sum-factorised (ncol 1,\n"
-              "# ks -3) or each as chosen (ncol 2)\n");
+              "# ks -3) or each as chosen (ncol 2), measured on the groups p.d.size_class in the last column\n");
   for (auto& kv : c)
-    fprintf(fh, "%s %d %d %d %d %d %.3f\n", kv.first.arch.c_str(), kv.first.p, kv.first.d, kv.first.size_class,
-            kv.second.ncol, kv.second.ks, kv.second.us);
+    fprintf(fh, "%s %d %d %d %d %d %.3f %d%s%s\n", kv.first.arch.c_str(), kv.first.p, kv.first.d, kv.first.size_class,
+            kv.second.ncol, kv.second.ks, kv.second.us, TILE_SET, kv.first.p == 0 ? " " : "", kv.first.groups.c_str());
   const bool ok = fclose(fh) == 0;
   return ok && std::rename(tmp.c_str(), path) == 0;
 }
@@ -2094,7 +2105,7 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
   const int cand_nc[3] = {1, 2, 4};
   const int cand_ks[5] = {0, 1, 2, 4, 8};  // 0: the LDS-staged contraction
   for (auto& g : P->groups) {
-    const TileKey key{arch, g.p, g.d, size_class(g.flops / (2.0 * g.S * g.ne * g.ne))};
+    const TileKey key{arch, g.p, g.d, size_class(g.flops / (2.0 * g.S * g.ne * g.ne)), ""};
     auto hit = cache.find(key);
     if (hit != cache.end() && hit->second.ks == -2 && P->prm.stored_matrices) {
       int rc = ensure_stored(P, g);
@@ -2243,8 +2254,17 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
   };
   {
     int64_t cols = 0;
-    for (auto& g : P->groups) cols += (int64_t)(g.flops / (2.0 * g.S * g.ne * g.ne));
-    const TileKey key{arch, 0, (int)P->groups.size(), size_class((double)cols)};
+    std::vector<std::array<int, 3>> pdc;  // the groups are in the order of the first element of each
+    for (auto& g : P->groups) {
+      const double n = g.flops / (2.0 * g.S * g.ne * g.ne);
+      cols += (int64_t)n;
+      pdc.push_back({g.p, g.d, size_class(n)});
+    }
+    std::sort(pdc.begin(), pdc.end());
+    std::string groups;
+    for (auto& [p, d, c] : pdc)
+      groups += (groups.empty() ? "" : ",") + std::to_string(p) + "." + std::to_string(d) + "." + std::to_string(c);
+    const TileKey key{arch, 0, (int)P->groups.size(), size_class((double)cols), groups};
     auto hit = cache.find(key);
     if (hit != cache.end()) {
       P->fused = hit->second.ncol == 1 && hit->second.ks == 0;
