@@ -340,8 +340,9 @@ int mto_autotune(mto_plan* plan, const double* rho, const char* cache_path, void
                  int32_t report_len);
 
 /* Sets the kernel and tile shape of the element product for the group with
- * order p and cell grid d (all groups if p <= 0).  A new plan takes ks = -3
- * for every group: the sum-factorised product (ncol ignored), which uses the
+ * order p and cell grid d (all groups if p <= 0).  A new plan on
+ * MTO_PATH_MFMA takes ks = -3 for every group: the sum-factorised product
+ * (ncol ignored; MTO_EINVAL on MTO_PATH_PLAIN), which uses the
  * tensor structure of the basis and of the cell grid instead of the dense
  * cell tables, every such group in one launch.  The dense contraction:
  * ncol blocks of 16 element columns
@@ -361,7 +362,7 @@ int mto_autotune(mto_plan* plan, const double* rho, const char* cache_path, void
  * contracting the cell tables; every load case of an instance shares one
  * read.  The product is HBM-bound instead of MFMA-bound; it is not part of
  * the one-launch product.  MTO_EINVAL if the shape needs more LDS than the
- * kernel takes (64 KB; 160 KB for ks = 0) or no group matches (ks = -2).
+ * kernel takes (64 KB; 160 KB for ks = 0) or no group matches (ks = -2, -3).
  * Invalidates captured graphs. */
 int mto_set_tile(mto_plan* plan, int32_t p, int32_t d, int32_t ncol, int32_t ks);
 

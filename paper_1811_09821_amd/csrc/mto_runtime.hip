@@ -2037,10 +2037,11 @@ int mto_set_tile(mto_plan* P, int32_t p, int32_t d, int32_t ncol, int32_t ks) {
     return rebuild_tiles(P);
   }
   if (P && ks == -3) {  // the sum-factorised product for the group(s)
+    if (P->prm.kernel_path != MTO_PATH_MFMA) return fail(MTO_EINVAL, "the sum-factorised product needs MTO_PATH_MFMA");
     bool any = false;
     for (auto& g : P->groups)
       if (p <= 0 || (g.p == p && g.d == d)) {
-        if (P->prm.kernel_path == MTO_PATH_MFMA) g.factored = 1;
+        g.factored = 1;
         g.stored = 0;
         any = true;
       }
