@@ -241,6 +241,12 @@ def tile_shapes(report):
     return sorted(out)
 
 
+def fused_product(report):
+    """Whether the plan's product is the fused contraction, whatever the kernels
+    of its groups ("chosen" lines) would be one by one."""
+    return any(ln.startswith("product: fused") for ln in report.splitlines())
+
+
 def run_workload(mto, args, config, prs, path, precond, steps, warmup, tune=True):
     """Plan, tile shapes, capture, `warmup` + `steps` timed replays of the
     whole step, then the contraction timings.  Returns the plan, the
@@ -271,11 +277,16 @@ def run_workload(mto, args, config, prs, path, precond, steps, warmup, tune=True
     return plan, res, rho, u
 
 
-def product_flops(prs, shapes):
+def factored_groups(shapes, fused):
+    """(p, d) of the groups whose product is sum-factorised (ks = -3)."""
+    return set() if fused else {tuple(int(v) for v in s.split()[:2]) for s in shapes if s.split()[3] == "-3"}
+
+
+def product_flops(prs, shapes, fused=False):
     """Useful flops of one product over all systems: dense contraction, 2 d^2
     (2 n^2)^2 per element and load case (n = p + 1), or, for the groups whose
-    product is sum-factorised (ks = -3), 2 d (16 n^3 + (2 n^2 + n) d)."""
-    factored = {tuple(int(v) for v in s.split()[:2]) for s in shapes if s.split()[3] == "-3"}
+    product is sum-factorised, 2 d (16 n^3 + (2 n^2 + n) d)."""
+    factored = factored_groups(shapes, fused)
     total = 0
     for pr in prs:
         for p, d in zip(pr.p, pr.d):
@@ -286,7 +297,20 @@ def product_flops(prs, shapes):
     return total
 
 
-def contraction_roofline(plan, prs, rho, stats, config, path_name, shapes):
+def product_kernel(shapes, fused):
+    """(bound, kernel) of the roofline, by what a product launches."""
+    n = len(factored_groups(shapes, fused))
+    if fused:
+        return "mfma", "k_elem_fused (element contraction of every (p, d) group, PCG search direction)"
+    if n == 0:
+        return "mfma", "k_elem_mfma (element contraction of every (p, d) group, PCG search direction)"
+    if n < len(shapes):
+        return ("fp64 vector fma / mfma", "k_elem_factored (sum-factorised groups) and the contraction of the other "
+                "groups, PCG search direction")
+    return "fp64 vector fma", "k_elem_factored (sum-factorised element product, PCG search direction)"
+
+
+def contraction_roofline(plan, prs, rho, stats, config, path_name, shapes, fused):
     """Roofline of the element product (one PCG product K p over all (p, d)
     groups): useful flops of one product, as carried out, over the mean
     duration of 100 back-to-back launches between two events on the plan's
@@ -297,13 +321,12 @@ def contraction_roofline(plan, prs, rho, stats, config, path_name, shapes):
     reps = max(1, min(100, it_min // 3))
     t_loop_ms = plan.time_contraction(rho, reps=reps, in_loop=True)
     t_mv_ms = plan.time_contraction(rho, reps=100)
-    flops = product_flops(prs, shapes) if shapes else plan.info["flops_per_matvec"]
-    factored = any(s.split()[3] == "-3" for s in shapes)
+    flops = product_flops(prs, shapes, fused) if shapes else plan.info["flops_per_matvec"]
+    bound, kernel = product_kernel(shapes, fused)
     achieved = flops / (t_mv_ms * 1e-3) / 1e12
-    return {"bound": "fp64 vector fma" if factored else "mfma", "achieved": round(achieved, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
+    return {"bound": bound, "achieved": round(achieved, 3), "peak": PEAK_FP64_MFMA_TFLOPS, "unit": "TFLOP/s",
             "frac": round(achieved / PEAK_FP64_MFMA_TFLOPS, 4), "traffic": traffic_for(config, shapes, path_name),
-            "kernel": "k_elem_factored (sum-factorised element product, PCG search direction)" if factored else
-            "k_elem_mfma (element contraction of every (p, d) group, PCG search direction)",
+            "kernel": kernel,
             "flops_per_launch": flops, "dense_flops_per_launch": plan.info["flops_per_matvec"], "ms_per_launch": round(t_mv_ms, 5), "launches_timed": 100,
             "ms_per_launch_in_pcg_loop": round(t_loop_ms, 5), "in_loop_reps": reps,
             "frac_in_pcg_loop": round(flops / (t_loop_ms * 1e-3) / 1e12 / PEAK_FP64_MFMA_TFLOPS, 4),
@@ -355,7 +378,7 @@ def contraction_only(args, prs, desc):
     report = plan.autotune(rho, cache=args.tile_cache or None)
     ms = plan.time_contraction(rho, reps=100)
     out = {"workload": desc, "ms_per_launch": ms, "tile_shapes": tile_shapes(report),
-           "flops_per_launch": product_flops(prs, tile_shapes(report))}
+           "flops_per_launch": product_flops(prs, tile_shapes(report), fused_product(report))}
     if args.calibrate_copy_mb > 0:
         n = args.calibrate_copy_mb * (1 << 20) // 8
         a = torch.ones(n, dtype=torch.float64, device="cuda:0")
@@ -437,7 +460,7 @@ def main():
     progress(f"config {args.config}: {res['s_per_design']:.6f} s/design; contraction roofline")
     stats = res["stats"]
     shapes = tile_shapes(res["report"])
-    roof = contraction_roofline(plan, prs, rho, stats, args.config, args.path, shapes)
+    roof = contraction_roofline(plan, prs, rho, stats, args.config, args.path, shapes, fused_product(res["report"]))
     its = stats["iterations"] if stats else None
 
     out = {
@@ -461,7 +484,7 @@ def main():
         {"min": min(its), "max": max(its), "mean": round(float(np.mean(its)), 2), "per_system": its},
         "true_rel_residual_max": max(stats["true_rel_residual"]) if stats else None,
         "restarts": stats["restarts"] if stats else None,
-        "contraction_mfma_pct_of_peak": roof["frac"] * 100,
+        "product_pct_of_fp64_peak": roof["frac"] * 100,
         "roofline": roof,
     }
     if res["report"]:
@@ -491,7 +514,8 @@ def main():
         prs2, desc2 = workload(2, args.eased_field)
         plan2, res2, rho2, _ = run_workload(mto, args, 2, prs2, path, precond, max(args.steps, 20), args.warmup)
         shapes2 = tile_shapes(res2["report"])
-        roof2 = contraction_roofline(plan2, prs2, rho2, res2["stats"], 2, args.path, shapes2)
+        roof2 = contraction_roofline(plan2, prs2, rho2, res2["stats"], 2, args.path, shapes2,
+                                     fused_product(res2["report"]))
         out["secondary"] = {"workload": desc2, "s_per_design": res2["s_per_design"],
                             "pcg_iterations": res2["stats"]["iterations"],
                             "true_rel_residual": res2["stats"]["true_rel_residual"],

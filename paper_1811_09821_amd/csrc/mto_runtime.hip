@@ -2316,9 +2316,13 @@ int mto_autotune(mto_plan* P, const double* rho, const char* cache_path, void* s
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   {
-    char line[96];
-    snprintf(line, sizeof line, "product: %s\n", P->fused ? "fused (one launch for all groups)" : "one launch per group");
-    rep += line;
+    size_t n_fac = 0;  // what enq_elem_all launches
+    for (auto& g : P->groups) n_fac += g.factored;
+    rep += std::string("product: ") +
+           (P->fused                      ? "fused (one launch for all groups)"
+            : n_fac == P->groups.size()   ? "sum-factorised (one launch for all groups)"
+            : n_fac > 0                   ? "one launch for the sum-factorised groups, one for each other group"
+                                          : "one launch per group") + "\n";
   }
   for (auto& g : P->groups) {
     char line[96];
