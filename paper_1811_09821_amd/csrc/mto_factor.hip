@@ -48,7 +48,7 @@ __host__ __device__ constexpr int sym_index(int n, int i, int k) {  // packed up
 }
 
 // acc += the product for the cell rows sy0, sy0 + step, ... of one column: u
-// its element vector in LDS (rigid motion removed; row r at 64 r), tab the
+// its element vector in LDS (rigid motion removed; row r at LS r), tab the
 // group's 1D tables.  NC = 2: both components; NC = 1: component c0 alone.
 // NK < n: u is nonzero only for the functions i, j < NK (the vertex
 // functions, NK = 2).
@@ -58,7 +58,7 @@ __host__ __device__ constexpr int sym_index(int n, int i, int k) {  // packed up
 // asm statements hold each pass together: without them the compiler keeps u
 // in registers across the passes, or sinks a pass's products below the next
 // loop with all their operands live, and spills.
-template <int P, int NK, int NC>
+template <int P, int NK, int NC, int LS = 64>
 __device__ __forceinline__ void factored_rows(int d, cptr tab, const double* __restrict__ Ecell, int sy0, int step,
                                               int c0, lds_vec u, double (&acc)[NC][P + 1][P + 1]) {
   constexpr int n = P + 1, NS = n * (n + 1) / 2, XT = fac_x_of(P), YT = fac_y_of(P);
@@ -87,7 +87,7 @@ __device__ __forceinline__ void factored_rows(int d, cptr tab, const double* __r
     auto pass = [&](int yo, bool swap, auto entry) {
       lds_vec up = u;
       asm volatile("" : "+v"(up));
-      if (NC == 1) up += 64 * (swap ? 1 - c0 : c0);
+      if (NC == 1) up += LS * (swap ? 1 - c0 : c0);
       cptr yc = ys + (NC == 1 ? yo + c0 : yo) * n;
       double ul[2][NK][NC], yv[2][NC][n];
       auto request = [&](int b, int l) {
@@ -98,7 +98,7 @@ __device__ __forceinline__ void factored_rows(int d, cptr tab, const double* __r
 #pragma unroll
         for (int k = 0; k < NK; ++k)
 #pragma unroll
-          for (int c = 0; c < NC; ++c) ul[b][k][c] = up[(2 * (l * n + k) + c) * 64];
+          for (int c = 0; c < NC; ++c) ul[b][k][c] = up[(2 * (l * n + k) + c) * LS];
       };
       request(0, 0);
 #pragma unroll
@@ -336,6 +336,120 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
   });
 }
 
+// One tile of at most FAC_NARROW = 16 columns by the four waves of a block, for
+// plans whose tiles are few (fac_cols): the launch is one tile's latency then.
+// Lane l holds column l % 16 and, in the gather and the scatter, row l / 16 of four
+// rows of an instruction, which are a quarter of a 64-column tile's
+// instructions; in between the lanes of the four sets compute the same sums, in
+// the order of the other tiles.  What depends on the tile alone is requested
+// before anything is waited for, the scatter slots (VERT: and their values) too,
+// and both components' partial results meet in LDS at once.
+//   Time of a product in the PCG loop, 2013 elements, a launch of 64-column tiles ->
+// of these (us): p = 4, d = 5: 27.0 -> 22.2; p = 3, d = 2: 11.1 -> 8.8 (the dense
+// contraction on its tiles of 16 columns: 29.8, 8.5).
+template <int P, bool VERT>
+__device__ __forceinline__ void narrow_tile(const FacTile& t, const double* __restrict__ E,
+                                            const double* __restrict__ xin, const PcgDev& s, int mode, int it_k,
+                                            double* ush) {
+  constexpr int n = P + 1, NE = ne_of(P), C = FAC_NARROW, RP = 64 / C, W = FAC_MAX_W;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = lane % C, r0 = wave * RP + lane / C;  // this lane's rows r0, r0 + W RP, ...
+  const bool pcg = mode == ELEM_PCG, valid = col < t.count;
+  const int el = valid ? col : t.count - 1;  // idle lanes repeat the last column, unstored
+  const double* __restrict__ xs = xin + t.dof_off;
+  const double* __restrict__ zs = s.z + t.dof_off;
+  constexpr int NG = VERT ? 8 : NE, GB = (NG + W * RP - 1) / (W * RP), SB = (NE + W * RP - 1) / (W * RP);
+  auto row_of = [](int k) { return VERT ? vertex_dof<P>(k) : k; };
+  int gi[GB], si[SB];
+#pragma unroll
+  for (int q = 0; q < GB; ++q) gi[q] = t.gidx[(int64_t)row_of(min(r0 + W * RP * q, NG - 1)) * t.npad + el];
+  const int cell = t.cell[el];
+#pragma unroll
+  for (int q = 0; q < SB; ++q) si[q] = t.sidx[(int64_t)min(r0 + W * RP * q, NE - 1) * t.npad + el];
+  const int it = pcg ? *s.it_base + it_k : 0;
+  // a stopped system has nothing to do (PCG mode also checks this iteration's residual below)
+  if (mode != ELEM_APPLY && s.status[t.sys] != SYS_RUNNING) return;
+  // the column's moduli, one read per cache line: on their way during the gather
+  double warm[5];
+#pragma unroll
+  for (int k = 0; k < 5; ++k) warm[k] = E[cell + min(16 * k, t.d * t.d - 1)];
+  double v[GB], z[GB];
+#pragma unroll
+  for (int q = 0; q < GB; ++q) {
+    const int gc = max(gi[q], 0);
+    v[q] = xs[gc];
+    z[q] = pcg ? zs[gc] : 0.0;
+  }
+  double beta = 0.0;
+  bool on = true;
+  if (pcg) {  // by every wave, while its values load
+    const Scal sc = pcg_state(s, t.sys, t.pc_begin, t.pc_end, it, true);
+    on = sc.active;  // the same in every wave
+    beta = sc.beta;
+  }
+#pragma unroll
+  for (int q = 0; q < GB; ++q) {
+    const int k = r0 + W * RP * q;
+    // p = z + beta p_old formed as k_dof1 stores it
+    if (k < NG) ush[row_of(k) * C + col] = gi[q] >= 0 ? (pcg ? fma(beta, v[q], z[q]) : v[q]) : 0.0;
+  }
+  // (an empty statement that uses them)
+  asm volatile("" ::"v"(warm[0]), "v"(warm[1]), "v"(warm[2]), "v"(warm[3]), "v"(warm[4]));
+  if (!on) return;
+  __syncthreads();
+  {  // rigid motion removed from the vertex rows
+    const double x0 = ush[col], x1 = ush[C + col], th = ush[3 * C + col] - x1;
+    __syncthreads();
+    if (r0 < 8) {
+      const int row = vertex_dof<P>(r0);
+      ush[row * C + col] = rigid_free<P>(ush[row * C + col], row, x0, x1, th);
+    }
+    __syncthreads();
+  }
+  constexpr int NK = VERT ? 2 : n;
+  const cptr tab = scalar_table(t.kfac);
+  const double* __restrict__ Ec = E + cell;
+  const lds_vec u = (lds_vec)(ush + col);
+  const int nch = fac_chains(t.d);
+  double* __restrict__ sl = s.slots + t.slot_off;
+  double old[VERT ? SB : 1];
+  if (VERT) {
+#pragma unroll
+    for (int q = 0; q < SB; ++q) old[VERT ? q : 0] = sl[max(si[q], 0)];
+  }
+  // partial results in LDS, [chain][NE][C]
+  auto put = [&](int ch, int c, const double (&a)[n][n]) {
+#pragma unroll
+    for (int q = 0; q < n * n; ++q) ush[(ch * NE + 2 * q + c) * C + col] = a[q / n][q % n];
+  };
+  if (2 * nch <= W) {  // one component of one chain per wave
+    const int ch = wave >> 1, c = wave & 1;
+    double acc[1][n][n];
+    clear<P, 1>(acc);
+    if (ch < nch) factored_rows<P, NK, 1, C>(t.d, tab, Ec, ch, nch, c, u, acc);
+    __syncthreads();  // u is no longer read
+    if (ch < nch) put(ch, c, acc[0]);
+  } else {
+    double acc[2][n][n];
+    clear<P, 2>(acc);
+    if (wave < nch) factored_rows<P, NK, 2, C>(t.d, tab, Ec, wave, nch, 0, u, acc);
+    __syncthreads();
+    if (wave < nch) {
+      put(wave, 0, acc[0]);
+      put(wave, 1, acc[1]);
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < SB; ++q) {
+    const int a = r0 + W * RP * q;
+    if (a >= NE) break;
+    double y = ush[a * C + col];
+    for (int ch = 1; ch < nch; ++ch) y += ush[(ch * NE + a) * C + col];
+    if (valid && si[q] >= 0) sl[si[q]] = VERT ? old[VERT ? q : 0] + y : y;
+  }
+}
+
 // Tiles of 64 columns from any group, PM the largest order among them: n_split split tiles, one per block, then n_whole
 // tiles of order <= 2, one per wave.  At most 256 registers: two waves per SIMD.
 template <int PM, bool VERT>
@@ -363,6 +477,22 @@ __global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_factored(const FacTi
   if constexpr (PM >= 2)
     if (t.p == 2) return factored_tile<2, true, VERT>(t, E, xin, s, mode, it_k, lds);
   factored_tile<1, true, VERT>(t, E, xin, s, mode, it_k, lds);
+}
+
+template <int PM, bool VERT>
+__global__ __launch_bounds__(64 * FAC_MAX_W, 2) void k_elem_narrow(const FacTile* __restrict__ tiles, int n_tiles,
+                                                                  int xcd_run, const double* __restrict__ E,
+                                                                  const double* __restrict__ xin, PcgDev s, int mode,
+                                                                  int it_k) {
+  extern __shared__ double lds[];
+  const FacTile t = tiles[xcd_tile(blockIdx.x, n_tiles, xcd_run)];
+  if constexpr (PM >= 4)
+    if (t.p == 4) return narrow_tile<4, VERT>(t, E, xin, s, mode, it_k, lds);
+  if constexpr (PM >= 3)
+    if (t.p == 3) return narrow_tile<3, VERT>(t, E, xin, s, mode, it_k, lds);
+  if constexpr (PM >= 2)
+    if (t.p == 2) return narrow_tile<2, VERT>(t, E, xin, s, mode, it_k, lds);
+  narrow_tile<1, VERT>(t, E, xin, s, mode, it_k, lds);
 }
 
 // Sensitivity: w_s = lam_e^T K_s u_e for every cell s of every column, g =
@@ -520,6 +650,18 @@ void launch_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run,
   const dim3 grid(blocks), block(64 * f.waves);
   const FacTile* tl = tiles + f.tile_begin;
   const uint32_t lds = (uint32_t)f.lds;
+  if (f.cols == FAC_NARROW) {
+    auto go = [&](auto k) {
+      launch_timed(k, grid, block, lds, st, ev0, ev1, tl, (int)f.n_split, xcd_run, E, xin, s, mode, it_k);
+    };
+    switch (f.p_max) {
+      case 1: go(k_elem_narrow<1, VERT>); break;
+      case 2: go(k_elem_narrow<2, VERT>); break;
+      case 3: go(k_elem_narrow<3, VERT>); break;
+      default: go(k_elem_narrow<4, VERT>); break;
+    }
+    return;
+  }
   auto go = [&](auto k) {
     launch_timed(k, grid, block, lds, st, ev0, ev1, tl, (int)f.n_split, (int)f.n_whole, xcd_run, E, xin, s, mode, it_k);
   };

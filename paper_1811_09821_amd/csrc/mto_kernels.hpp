@@ -197,11 +197,12 @@ void launch_elem(const GroupDev& g, int path, const Tile* tiles, const double* E
 void launch_elem_fused(const GroupDev* groups, const Tile* tiles, int tile_begin, int n_tiles, int xcd_run,
                        size_t lds_bytes, const double* E, const double* xin, const PcgDev& s, int mode, int it_k,
                        hipStream_t st, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr);
-// One launch of the sum-factorised product (mto_factor.hip): tiles of 64
-// columns from tile_begin on, n_split of them
+// One launch of the sum-factorised product (mto_factor.hip): tiles of `cols`
+// columns (64 or FAC_NARROW) from tile_begin on, n_split of them
 // split over the `waves` waves of a block, then n_whole taken one per wave;
 // p_max: the largest order among their groups.
 constexpr int FAC_MAX_W = 4;
+constexpr int FAC_NARROW = 16;
 // Chains of the cell rows of a d x d grid (see mto_factor.hip): at most one
 // per wave, as even as that allows.
 __host__ __device__ constexpr int fac_chains(int d) {
@@ -218,13 +219,13 @@ struct FacTile {
   int32_t npad, count, sys, pc_begin, pc_end, p, d, group;
 };
 struct FactoredLaunch {
-  int32_t tile_begin, n_split, n_whole, p_max, waves;
+  int32_t tile_begin, n_split, n_whole, p_max, waves, cols;
   size_t lds;
 };
-inline size_t fac_lds_bytes(int p, int d, int waves, bool split) {
-  // partial results of both components at once for p <= 2, of one at a time above
-  const int ch = fac_chains(d) * (p <= 2 ? 2 : 1);
-  return 8 * (size_t)(split ? (ch > 2 ? ch : 2) * 32 : waves * 64) * ne_of(p);
+inline size_t fac_lds_bytes(int p, int d, int waves, bool split, int cols) {
+  // partial results of both components at once for p <= 2 or narrow tiles, of one at a time otherwise
+  const int ch = fac_chains(d) * (p <= 2 || cols == FAC_NARROW ? 2 : 1);
+  return 8 * (size_t)(split ? (ch > 2 ? ch : 2) * (cols / 2) : waves * 64) * ne_of(p);
 }
 void launch_elem_factored(const FacTile* tiles, const FactoredLaunch& f, int xcd_run,
                           const double* E, const double* xin, const PcgDev& s, int mode, int it_k, hipStream_t st,

@@ -319,6 +319,24 @@ void destroy_graphs(mto_plan* P) {
 // and functions for one wave to be done with it about as fast as its gather.
 bool may_go_whole(const GroupHost& g) { return g.p <= 2 && g.d <= 5; }
 
+// Columns of the sum-factorised kernels' tiles: 64, or 16 (FAC_NARROW) where the whole plan
+// has at most 256 such tiles, one per CU: the launch is one tile's latency then,
+// and a narrow tile gathers and scatters in a quarter of the instructions (p = 4,
+// d = 5, 2013 elements: 20.6 -> 17.9 us; p = 3, d = 2: 8.9 -> 6.8).  Two tiles to a
+// CU still pay where a wave has one row of cells, in orders whose gather is long
+// (6050 elements, p = 3, d = 2: 9.1 -> 8.5; but p = 4, d = 5: 20.9 -> 25.0, p = 2, d = 2:
+// 6.4 -> 6.7); four do not (12800, p = 3, d = 2: 9.8 -> 15.0).
+int fac_cols(const mto_plan* P) {
+  int64_t n = 0;
+  int p_max = 0, d_max = 0;
+  for (const GroupHost& g : P->groups) {
+    for (int i = 0; i < P->n_inst; ++i) n += (int64_t)P->L[i] * ((g.inst_begin[i + 1] - g.inst_begin[i] + FAC_NARROW - 1) / FAC_NARROW);
+    p_max = std::max(p_max, g.p);
+    d_max = std::max(d_max, g.d);
+  }
+  return n <= (p_max >= 3 && d_max <= 2 ? 512 : 256) ? FAC_NARROW : 64;
+}
+
 // The sum-factorised launch of groups gs (their tiles consecutive, in this
 // order, those that may go whole last).
 //   Up to 256 tiles (one per CU) every tile is split over four waves: the
@@ -329,12 +347,13 @@ bool may_go_whole(const GroupHost& g) { return g.p <= 2 && g.d <= 5; }
 //   More than 256 split tiles fill the chip by themselves and take one wave
 // per chain of cell rows, the least that keeps chains apart (400 x 200, 783
 // p = 4 tiles: 73 us; 82 with four waves).
-FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs) {
+FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs, int cols) {
   FactoredLaunch f{};
   f.waves = 4;
+  f.cols = cols;
   int total = 0, n_chains = 0;
   for (auto* g : gs) total += g->fac_n_tiles;
-  auto whole = [&](const GroupHost* g) { return total > 256 && may_go_whole(*g); };
+  auto whole = [&](const GroupHost* g) { return cols == 64 && total > 256 && may_go_whole(*g); };
   for (auto* g : gs) {
     if (g->fac_n_tiles == 0) continue;
     if (f.n_split + f.n_whole == 0) f.tile_begin = g->fac_tile_begin;
@@ -342,9 +361,9 @@ FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs) {
     if (!whole(g)) n_chains = std::max(n_chains, fac_chains(g->d));
     f.p_max = std::max(f.p_max, g->p);
   }
-  if (n_chains > 0 && f.n_split > 256) f.waves = n_chains;
+  if (cols == 64 && n_chains > 0 && f.n_split > 256) f.waves = n_chains;
   for (auto* g : gs)
-    f.lds = std::max(f.lds, fac_lds_bytes(whole(g) ? std::min(f.p_max, 2) : g->p, g->d, f.waves, !whole(g)));
+    f.lds = std::max(f.lds, fac_lds_bytes(whole(g) ? std::min(f.p_max, 2) : g->p, g->d, f.waves, !whole(g), cols));
   return f;
 }
 
@@ -435,8 +454,9 @@ int rebuild_tiles(mto_plan* P) {
     P->fused_n_tiles = (int)P->tiles.size() - P->fused_tile_begin;
   }
   {
-    // the same 64-column tiles for the sum-factorised kernels (their descriptors carry the group's
-    // arrays): the tiles that may go one to a wave last, the rest by decreasing work
+    // tiles for the sum-factorised kernels (their descriptors carry the group's arrays): the tiles that
+    // may go one to a wave last, the rest by decreasing work
+    const int cols = fac_cols(P);
     std::vector<int> order(P->groups.size());
     for (size_t k = 0; k < order.size(); ++k) order[k] = (int)k;
     std::stable_sort(order.begin(), order.end(), [&](int x, int y) {
@@ -454,14 +474,14 @@ int rebuild_tiles(mto_plan* P) {
           for (int l = 0; l < P->L[i]; ++l) {
             const int sysi = (int)P->c_off[i] + l;  // systems are numbered instance-major, like c
             const SysDesc& sd = P->sys[sysi];
-            for (int e = g.inst_begin[i]; e < g.inst_begin[i + 1]; e += 64)
+            for (int e = g.inst_begin[i]; e < g.inst_begin[i + 1]; e += cols)
               ft.push_back(FacTile{g.gidx + e, g.sidx + e, g.cell + e, g.kfac, sd.dof_off, sd.slot_off, g.npad,
-                                   std::min(64, g.inst_begin[i + 1] - e), sysi, sd.chunk_begin, sd.chunk_end, g.p, g.d, gi});
+                                   std::min(cols, g.inst_begin[i + 1] - e), sysi, sd.chunk_begin, sd.chunk_end, g.p, g.d, gi});
           }
         g.fac_n_tiles = (int)ft.size() - g.fac_tile_begin;
         gs.push_back(&g);
       }
-      return factored_launch(gs);
+      return factored_launch(gs, cols);
     };
     P->fac_all = tiles_of(order);
     std::vector<int> sub;
@@ -1135,7 +1155,7 @@ int build_plan(const mto_problem* probs, int n, const mto_params* prm, mto_plan*
 void enq_elem_group(mto_plan* P, const GroupHost& g, const double* xin, int mode, int it_k, hipStream_t st,
                     hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr) {
   if (g.factored) {
-    launch_elem_factored(P->d_fac_tiles, factored_launch({&g}), P->n_sys > 1 ? 8 : 0, P->E, xin, P->pcg(),
+    launch_elem_factored(P->d_fac_tiles, factored_launch({&g}, P->fac_all.cols), P->n_sys > 1 ? 8 : 0, P->E, xin, P->pcg(),
                          mode, it_k, st, ev0, ev1);
   } else if (g.stored && P->prm.kernel_path == MTO_PATH_MFMA)
     launch_elem_stored(P->gdev(g), P->d_tiles, xin, P->pcg(), mode, it_k, st, ev0, ev1);
