@@ -685,17 +685,23 @@ void launch_vertex_factored(const FacTile* tiles, const FactoredLaunch& f, int x
   launch_factored<true>(tiles, f, xcd_run, E, dz, s, ELEM_APPLY_RUNNING, 0, st, nullptr, nullptr);
 }
 
-// Up to 256 tiles (one per CU) each row of cells has its own wave; beyond, a
-// wave takes two, which keeps more columns' gathers in flight.  Measured (us),
-// a dense K_s contraction per cell and a launch per group -> this:
-//   160 x 80 mesh, p = 3, d = 4: 21.9 -> 9.4 (half of it the gather)
-//   400 x 200 mesh, p = 1..4, three systems: 250 -> 60
-//   16 designs, p = 4 in the main, two systems: 560 -> 158
+// Up to 256 tiles (one per CU) each row of cells has its own wave, and at least
+// four share the gather; up to 2048 four waves; beyond, two, which keep more columns'
+// gathers in flight.  us with 2, 4 and a wave per row of cells (at 256 and 2048 the
+// lines do not matter much, p = 4, d = 2 would take two waves from 700 tiles on):
+//   16 x 8 mesh, p = 4, d = 1: 12.5, 11.6 and 14.7
+//   110 x 55, p = 4, d = 5, 95 tiles: 27.6, 21.0 and 18.1
+//   300 x 150, p = 3, d = 4, 704 tiles: 30.6, 23.4 and 23.4
+//   400 x 200, p = 4, d = 5, 1250 tiles: 73.9, 70.7 and 85.2
+//   400 x 200, p = 1..4, three systems, 3750 tiles: 58.0, 67.6 and 99.4
+//   16 designs, p = 4 in the main, two systems, 9600 tiles: 136, 161 and 243
+// A dense K_s contraction per cell and a launch per group took 21.9 us on a 160 x 80
+// mesh, p = 3, d = 4 (now 9.4, half of it the gather), 250 and 560 on the last two.
 void launch_sens(const FacTile* tiles, const FactoredLaunch& f, int d_max, int xcd_run, const double* dE,
                  const double* x, const double* y, double* gout, const SysDesc* sys, hipStream_t st) {
   const int n = f.n_split + f.n_whole;
   if (n == 0) return;
-  const int waves = std::min(n <= 256 ? d_max : (d_max + 1) / 2, SENS_MAX_W);
+  const int waves = n <= 256 ? std::min(std::max(d_max, 4), SENS_MAX_W) : n <= 2048 ? 4 : 2;
   const bool same = x == y;
   const dim3 grid(n), block(64 * waves);
   const uint32_t lds = (uint32_t)(8 * 64 * ne_of(f.p_max) * (same ? 1 : 2));
