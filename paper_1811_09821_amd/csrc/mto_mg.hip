@@ -1300,14 +1300,16 @@ __global__ __launch_bounds__(64, 2) void k_asm_invert(const int32_t* __restrict_
 //   16 designs, p = 4 in the main, two systems: 245 on average -> 178
 //   160 x 80 mesh, p = 3, one system: 17.3 -> 11.6 / 14.7
 // (2.3-3.7 TB/s over the blocks; three waves per SIMD with the entries taken in
-// two parts spilled and lost.)  A launch of at least ASM_PERSIST blocks takes a
-// bounded grid: late in a batch most systems have stopped, and one look at 64
-// tiles costs less than 64 waves that start and end.
+// two parts spilled and lost.)  A launch takes at most ASM_GRID blocks: late in a
+// batch most systems have stopped, and one look at 64 tiles costs less than 64
+// waves that start and end.  The whole solve in ms with a wave per tile, with 4096,
+// 1024 and 256 blocks: 64 designs (48352 blocks) 371.6, 367.8, 371.8 and 379.9; 16
+// designs (13135) 125.5, 125.8, 126.4 and 130.8; 300 x 150, p = 4, d = 2, one system
+// (5625) 31.8, 32.1, 32.1 and 33.4.
 constexpr int ASM_SYS = 4;
 constexpr int ASM_WAVES = 4;      // waves per block
 constexpr int ASM_YS = 65;        // row stride of the partial sums in LDS
-constexpr int ASM_GRID = 1024;    // blocks of a persistent launch
-constexpr int ASM_PERSIST = 4096;  // ... for launches of at least this many
+constexpr int ASM_GRID = 4096;    // blocks of a launch at most
 
 // LDS doubles of a wave: the tile's element vectors, then the partial sums
 __host__ __device__ constexpr int asm_lds_of(int p) { return 128 + 4 * (p + 1) * ASM_YS; }
@@ -1576,13 +1578,13 @@ void launch_asm_block(const GroupDev& g, int gi, const GroupDev* groups, const i
   }
 }
 
-// One block per ASM_WAVES tiles, or the bounded grid.  MTO_ASM_GRID (a positive
+// One block per ASM_WAVES tiles, up to ASM_GRID blocks.  MTO_ASM_GRID (a positive
 // integer) caps the count: the results do not depend on it (every tile is
 // summed the same way by whichever wave takes it), which lets tests walk the
 // tiles of small meshes as the bounded grid walks those of large ones.
 int asm_apply_blocks(int n_tiles) {
   const int nb = (n_tiles + ASM_WAVES - 1) / ASM_WAVES;
-  int blocks = nb >= ASM_PERSIST ? ASM_GRID : nb;
+  int blocks = std::min(nb, ASM_GRID);
   if (const char* cap = std::getenv("MTO_ASM_GRID")) {
     const int c = std::atoi(cap);
     if (c > 0) blocks = std::min(blocks, c);

@@ -26,13 +26,13 @@ def blocks(n_tiles):
 
 
 def test_blocks_of_a_launch(monkeypatch):
-    """A block per four tiles below 4096 blocks, 1024 from there on, never more
-    than the cap; what is not a positive number caps nothing."""
+    """A block per four tiles, at most 4096 blocks, never more than the cap; what
+    is not a positive number caps nothing."""
     monkeypatch.delenv("MTO_ASM_GRID", raising=False)
-    assert [blocks(n) for n in (1, 4, 5, 16380, 16381, 10**6)] == [1, 1, 2, 4095, 1024, 1024]
+    assert [blocks(n) for n in (1, 4, 5, 16380, 16384, 16385, 10**6)] == [1, 1, 2, 4095, 4096, 4096, 4096]
     for cap in ("0", "-3", "x", ""):
         monkeypatch.setenv("MTO_ASM_GRID", cap)
-        assert [blocks(n) for n in (5, 16381)] == [2, 1024]
+        assert [blocks(n) for n in (5, 16385)] == [2, 4096]
     monkeypatch.setenv("MTO_ASM_GRID", "5")
     assert [blocks(n) for n in (1, 16, 20, 21, 16381)] == [1, 4, 5, 5, 5]
 
