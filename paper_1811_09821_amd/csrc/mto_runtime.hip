@@ -346,7 +346,10 @@ int fac_cols(const mto_plan* P) {
 // ones wait for (254 of the 314 tiles of that mesh: 21 against 42 us).
 //   More than 256 split tiles fill the chip by themselves and take one wave
 // per chain of cell rows, the least that keeps chains apart (400 x 200, 783
-// p = 4 tiles: 73 us; 82 with four waves).
+// p = 4 tiles: 73 us; 82 with four waves).  Where all tiles go whole they go one
+// to a block, which spreads them over the CUs as evenly as they can be (us with four
+// to a block and one, p = 1, d = 1: 400 x 200 9.1 and 8.6; p = 2, d = 5: 200 x 100 18.2
+// and 15.8).
 FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs, int cols) {
   FactoredLaunch f{};
   f.waves = 4;
@@ -362,6 +365,7 @@ FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs, int cols
     f.p_max = std::max(f.p_max, g->p);
   }
   if (cols == 64 && n_chains > 0 && f.n_split > 256) f.waves = n_chains;
+  if (f.n_split == 0 && f.n_whole > 0) f.waves = 1;
   for (auto* g : gs)
     f.lds = std::max(f.lds, fac_lds_bytes(whole(g) ? std::min(f.p_max, 2) : g->p, g->d, f.waves, !whole(g), cols));
   return f;
