@@ -62,12 +62,27 @@ constexpr int FBATCH = 8;
 constexpr int FTAB = 512;  // table entries held in LDS
 enum { F_PLAIN, F_PACKED, F_PACKED_LDS };
 
+// The pattern, as one argument (a launch costs the host some 50 ns for each).
+struct FilterDev {
+  const int64_t* sp;
+  const uint32_t* word;
+  const double* tab;
+  const int32_t* col;
+  const double *h, *s;
+  int64_t n;
+  int32_t n_tab;
+};
+
 template <bool GRAD, int FORM>
-__global__ __launch_bounds__(256) void k_filter(const int64_t* __restrict__ sp, const uint32_t* __restrict__ word,
-                                                const double* __restrict__ tab, int n_tab,
-                                                const int32_t* __restrict__ col, const double* __restrict__ h,
-                                                const double* __restrict__ s, const double* __restrict__ x,
-                                                double* __restrict__ y, int64_t n) {
+__global__ __launch_bounds__(256) void k_filter(FilterDev f, const double* __restrict__ x, double* __restrict__ y) {
+  const int64_t* __restrict__ sp = f.sp;
+  const uint32_t* __restrict__ word = f.word;
+  const double* __restrict__ tab = f.tab;
+  const int32_t* __restrict__ col = f.col;
+  const double* __restrict__ h = f.h;
+  const double* __restrict__ s = f.s;
+  const int64_t n = f.n;
+  const int n_tab = f.n_tab;
   __shared__ double tl[FORM == F_PACKED_LDS ? FTAB : 1];
   // consecutive blocks go to the XCDs in turn: each XCD takes a contiguous
   // eighth of the rows, whose x its L2 then holds
@@ -148,8 +163,8 @@ int launch(const mto_filter* F, bool grad, const double* x, double* y, void* str
     return set_error(MTO_EINVAL, "density filter used on a device other than the one it was created on");
   const unsigned blocks = (unsigned)((F->n + 255) / 256 + 7) / 8 * 8;
   auto go = [&](auto k) {
-    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, (hipStream_t)stream, F->sp, F->word, F->tab, F->n_tab, F->col,
-                       F->h, F->s, x, y, F->n);
+    hipLaunchKernelGGL(k, dim3(blocks), dim3(256), 0, (hipStream_t)stream,
+                       FilterDev{F->sp, F->word, F->tab, F->col, F->h, F->s, F->n, F->n_tab}, x, y);
   };
   if (!F->word)
     grad ? go(k_filter<true, F_PLAIN>) : go(k_filter<false, F_PLAIN>);
