@@ -48,8 +48,6 @@ constexpr int asm_tile_of(int p) { return ((p + 1) * (2 * p + 3) + 1) / 2 * 2 * 
 // interval, input function l), of the y factors (8 columns of n = p + 1).
 constexpr int fac_x_of(int p) { return (p + 1) * (p + 2) + (p + 1) * (p + 1); }
 constexpr int fac_y_of(int p) { return 8 * (p + 1); }
-// Their length, padded to whole 1 KB copies.
-constexpr int fac_table_of(int p, int d) { return (d * (fac_x_of(p) + (p + 1) * fac_y_of(p)) + 127) / 128 * 128; }
 
 // Host-side K_s tables of Appendix B's composite integration:
 // ks[s*ne*ne + i*ne + j] for density cell s of a d x d grid.
@@ -90,7 +88,7 @@ std::vector<double> staged_fragments(const std::vector<double>& ks, int p, int d
 // a packed (upper triangle by rows), b packed, c [i][k]; then
 // [d][l = 0..p][8][j = 0..p], the y factors with the plane-stress constants
 // folded in: D11 b(j,l), D33 b(j,l), D33 a(j,l), D11 a(j,l), D12 c(l,j),
-// D33 c(l,j), D33 c(j,l), D12 c(j,l); zeros up to fac_table_of(p, d).  Long
+// D33 c(l,j), D33 c(j,l), D12 c(j,l).  Long
 // double, rounded once.
 std::vector<double> factor_tables(int p, int d, double nu);
 

@@ -636,7 +636,7 @@ __global__ __launch_bounds__(256) void k_elem_assemble(GroupDev g, const double*
 // The product with stored element matrices: slots = K_e (x_e - rigid motion)
 // for every system of an instance from one read of K_e.  One block of 256
 // threads per tile of EB = asm_cols_of(P) element columns of an instance's
-// first system (the tiles of the Schwarz application), thread (column c,
+// first system, thread (column c,
 // row a) for the first NE EB threads.  The tile's triangles are one
 // contiguous range, loaded with 16-byte loads and staged in LDS while the
 // element vectors are gathered (PCG mode: p = z + beta p_old formed as

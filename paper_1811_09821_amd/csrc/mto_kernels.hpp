@@ -43,7 +43,6 @@ struct GroupDev {
   const double* kst;       // stored element matrices K_e (stored != 0): [npad][asm_ntp_of(p)] packed upper triangles
   int32_t stored;          // products of this group read kst (k_elem_stored) instead of contracting K_s
   const double* ks;        // plain K_s [S][ne][ne]
-  const double* kfac;      // 1D tables of the sum-factorised product (factor_tables)
   const double* kdiag;     // diag(K_s) [S][ne]
   const double* kabs;      // row sums of |K_s| [S][ne] (l1 smoother)
   const int32_t* gidx;     // [NEP][npad] free DOF (instance-local) of local DOF, -1 absent
@@ -214,7 +213,7 @@ struct FacTile {
   const int32_t* gidx;   // [NEP][npad], [NE][npad], [npad] as in GroupDev
   const int32_t* sidx;
   const int32_t* cell;
-  const double* kfac;
+  const double* kfac;    // 1D tables of the sum-factorised kernels (factor_tables)
   int64_t dof_off, slot_off;
   int32_t npad, count, sys, pc_begin, pc_end, p, d, group;
 };

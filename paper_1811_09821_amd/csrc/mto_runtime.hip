@@ -68,7 +68,7 @@ struct GroupHost {
   int n_elems = 0, npad = 0, ncol = 1, waves = 1;
   // LDS-staged contraction (p >= 3): 0 = off, else 64 lds_nc columns per tile, on their own tiles
   int lds_nc = 0, lds_tile_begin = 0, lds_n_tiles = 0;
-  // tiles of the first system of each instance (the Schwarz application serves all its systems)
+  // tiles of the first system of each instance (the stored-matrix product serves all its systems)
   int ms_tile_begin = 0, ms_n_tiles = 0;
   // per instance: element range [inst_begin[i], inst_begin[i+1]) in the group arrays
   std::vector<int32_t> inst_begin;
@@ -272,7 +272,6 @@ struct mto_plan {
     o.kfrags = g.kfrags ? g.kfrags : g.kfrag;
     o.kst = g.kst;
     o.stored = g.stored;
-    o.kfac = g.kfac;
     o.ks = g.ks;
     o.kdiag = g.kdiag;
     o.kabs = g.kabs;
@@ -373,8 +372,9 @@ FactoredLaunch factored_launch(const std::vector<const GroupHost*>& gs, int cols
 
 // Tiles for every group with its current ncol, then the tiles of the
 // LDS-staged contraction (64 lds_nc columns) for the groups that use it, then
-// the tiles of the first system of every instance (16 ncol columns) for the
-// Schwarz application; uploads them.
+// the tiles of the first system of every instance (asm_cols_of(p) columns) for
+// the stored-matrix product, the fused contraction's and the sum-factorised
+// kernels'; uploads them.
 int rebuild_tiles(mto_plan* P) {
   P->tiles.clear();
   for (int pass = 0; pass < 3; ++pass)
@@ -407,7 +407,7 @@ int rebuild_tiles(mto_plan* P) {
           t.sys = sysi;
           t.elem_begin = e;
           t.count = std::min(tile_cols, b - e);
-          t.pc_begin = pass == 2 ? P->L[i] : sd.chunk_begin;  // Schwarz tiles: the instance's system count
+          t.pc_begin = pass == 2 ? P->L[i] : sd.chunk_begin;  // pass 2: the instance's system count
           t.pc_end = sd.chunk_end;
           P->tiles.push_back(t);
         }
@@ -836,6 +836,7 @@ int build_asm(mto_plan* P, const std::vector<InstanceHost>& I) {
           }
       }
     }
+    // (offsets into the tiles are 64-bit; larger groups, 1.7 10^6 elements at p = 4, have not been run)
     if ((int64_t)G.ne * (G.ne + 1) / 2 * G.npad >= ((int64_t)1 << 31))
       return fail(MTO_EINVAL, "Schwarz smoother: too many elements of one (p, d) group for 32-bit block offsets");
     // tiles of asm_elems_of(p) columns, each instance's starting its own

@@ -123,7 +123,7 @@ std::vector<double> subcell_tables(int p, int d, double nu) {
 
 std::vector<double> factor_tables(int p, int d, double nu) {
   const int n = p + 1, X = fac_x_of(p), Y = fac_y_of(p);
-  std::vector<double> out((size_t)fac_table_of(p, d), 0.0);
+  std::vector<double> out((size_t)d * (X + n * Y), 0.0);
   const ld q = 1.0L / (1.0L - (ld)nu * nu), D11 = q, D12 = q * nu, D33 = q * (1 - (ld)nu) / 2;
   ld gx[16], gw[16];
   gauss_legendre(n, gx, gw);
