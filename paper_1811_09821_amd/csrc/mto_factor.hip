@@ -28,7 +28,8 @@
 // block of W waves, one chain (or, with waves to spare, one component of one
 // chain) to a wave, which share the gather and the scatter and meet in LDS.
 // The other tiles (small elements of large meshes) go one to a wave, from
-// gather to scatter without a barrier, W of them to a block.
+// gather to scatter without a barrier, W of them to a block.  Plans of few tiles
+// take tiles of 16 columns instead (narrow_tile).
 
 #include <hip/hip_runtime.h>
 
@@ -345,7 +346,7 @@ __device__ __forceinline__ void factored_tile(const FacTile& t, const double* __
 // before anything is waited for, the scatter slots (VERT: and their values) too,
 // and both components' partial results meet in LDS at once.
 //   Time of a product in the PCG loop, 2013 elements, a launch of 64-column tiles ->
-// of these (us): p = 4, d = 5: 27.0 -> 22.2; p = 3, d = 2: 11.1 -> 8.8 (the dense
+// of these (us): p = 4, d = 5: 27.0 -> 21.9; p = 3, d = 2: 11.1 -> 8.6 (the dense
 // contraction on its tiles of 16 columns: 29.8, 8.5).
 template <int P, bool VERT>
 __device__ __forceinline__ void narrow_tile(const FacTile& t, const double* __restrict__ E,

@@ -321,7 +321,7 @@ bool may_go_whole(const GroupHost& g) { return g.p <= 2 && g.d <= 5; }
 // Columns of the sum-factorised kernels' tiles: 64, or 16 (FAC_NARROW) where the whole plan
 // has at most 256 such tiles, one per CU: the launch is one tile's latency then,
 // and a narrow tile gathers and scatters in a quarter of the instructions (p = 4,
-// d = 5, 2013 elements: 20.6 -> 17.9 us; p = 3, d = 2: 8.9 -> 6.8).  Two tiles to a
+// d = 5, 2013 elements: 20.6 -> 17.9 us; p = 3, d = 2: 8.9 -> 6.6).  Two tiles to a
 // CU still pay where a wave has one row of cells, in orders whose gather is long
 // (6050 elements, p = 3, d = 2: 9.1 -> 8.5; but p = 4, d = 5: 20.9 -> 25.0, p = 2, d = 2:
 // 6.4 -> 6.7); four do not (12800, p = 3, d = 2: 9.8 -> 15.0).
