@@ -32,16 +32,18 @@ def vector(pr, seed):
     return x.ravel(), ref.ravel()
 
 
-def filler():
-    """9000 elements: 563 narrow tiles by itself."""
-    return P.uniform_random(100, 90, 1, 1, seed=1, lo=0.4)
+def filler(large):
+    """4224 or 17600 elements: 264 or 1100 narrow tiles by itself, so that the
+    plan takes tiles of 64 columns, 66 (each split over four waves) or 275."""
+    nelx, nely = (160, 110) if large else (66, 64)
+    return P.uniform_random(nelx, nely, 3, 3, seed=1, lo=0.4)
 
 
 def check(pr, cuda, seed):
-    """Alone and beside the filler, against the oracle and each other."""
+    """Alone and beside each filler, against the oracle and each other."""
     x, ref = vector(pr, seed)
     out = []
-    for prs in ([pr], [pr, filler()]):
+    for prs in ([pr], [pr, filler(False)], [pr, filler(True)]):
         plan = mto().Plan(prs)
         rho = torch.tensor(np.concatenate([q.rho for q in prs]), device=cuda)
         xs = torch.zeros(plan.info["n_u"], dtype=torch.float64, device=cuda)
@@ -50,8 +52,9 @@ def check(pr, cuda, seed):
         err = np.linalg.norm(y.cpu().numpy() - ref) / np.linalg.norm(ref)
         assert err < 1e-13, (pr.name, len(prs), err)
         out.append((y, plan.sensitivity(rho, xs)[:pr.n_cells * pr.n_load_cases], plan.jacobi_diagonal(rho)))
-    for a, b in zip(*out):
-        assert torch.equal(a, b[:a.numel()])
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert torch.equal(a, b[:a.numel()])
 
 
 @pytest.mark.parametrize("p,d", [(p, d) for p in (1, 2, 3, 4) for d in range(1, 9)])
